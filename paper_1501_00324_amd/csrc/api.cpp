@@ -24,6 +24,7 @@ void free_handle(fs_csr *A)
     dfree(A->d_val_bf16); dfree(A->d_col); dfree(A->d_map); dfree(A->d_imap);
     dfree(A->d_jpos); dfree(A->d_rstart);
     dfree(A->d_col16); dfree(A->d_gbase);
+    dfree(A->d_sgrp); dfree(A->d_loc); dfree(A->d_lpat); dfree(A->d_scols);
     dfree(A->d_perm); dfree(A->d_iperm); dfree(A->d_xtmp); dfree(A->d_Xtmp);
 }
 
@@ -105,6 +106,78 @@ fs_status build_refresh_rows(fs_csr *A, const int32_t *h_rp, int64_t &acct,
     FS_TRY(dalloc(&A->d_rstart, A->n_rows, acct));
     FS_HIP_TRY(launch_refresh_rows(A->d_groups, A->n_groups, A->host.vec,
                                    A->d_imap, A->d_jpos, A->d_rstart, s));
+    return FS_OK;
+}
+
+// Arrays of the staged products (internal.h: StageGroup), kept when every
+// group has at most kStageMax distinct columns and the matrix at most
+// kStageMost of them per slot: a staged group gathers each column once
+// instead of once per slot, and reads its list on top.  After the slot
+// columns (and 16-bit bases) are set, on the same stream, which it
+// synchronises.
+fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
+{
+    const size_t ng = size_t(A->n_groups);
+    if (ng == 0 || A->slots == 0) return FS_OK;
+    const bool narrow = A->d_gbase != nullptr;
+    int64_t bytes = 0;
+    int2 *d_counts = nullptr;
+    FS_TRY(dalloc(&d_counts, A->n_groups, bytes));
+    struct Scratch {
+        int2 *&p;
+        ~Scratch() { dfree(p); }
+    } scratch{d_counts};
+    bytes = 0;
+    FS_TRY(dalloc(&A->d_lpat, int64_t(ng) * kWave, bytes));
+    FS_HIP_TRY(launch_stage_count(A->d_groups, A->n_groups, A->host.vec,
+                                  A->d_col, narrow, A->d_lpat, d_counts, s));
+    std::vector<int2> cnt(ng);
+    FS_HIP_TRY(hipMemcpyAsync(cnt.data(), d_counts, sizeof(int2) * ng,
+                              hipMemcpyDeviceToHost, s));
+    FS_HIP_TRY(hipStreamSynchronize(s));
+    std::vector<StageGroup> grp(ng);
+    int64_t loc = 0, list = 0;
+    int32_t most = 0;
+    for (size_t g = 0; g < ng; ++g) {
+        const int32_t wl = A->host.groups[g].width_lt;
+        const int32_t per = cnt[g].x << (wl >> 24), nd = cnt[g].y;
+        most = nd < 0 ? INT32_MAX : std::max(most, nd);
+        if (most > kStageMax) break;
+        grp[g] = StageGroup{int32_t(loc), per, int32_t(list), nd};
+        loc += int64_t(per) * (((wl & 0xffffff) + 3) / 4);
+        list += nd;
+    }
+    if (most > kStageMax || double(list) > kStageMost * double(A->slots)) {
+        dfree(A->d_lpat);
+        return FS_OK;
+    }
+    char *cols = nullptr;
+    fs_status st = dalloc(&A->d_loc, 4 * loc, bytes);
+    if (st == FS_OK) st = dalloc(&cols, list * (narrow ? 2 : 4), bytes);
+    A->d_scols = cols;
+    if (st == FS_OK) st = dalloc(&A->d_sgrp, A->n_groups, bytes);
+    if (st != FS_OK) {
+        // no room: the unstaged products need none of it
+        dfree(A->d_lpat);
+        dfree(A->d_loc);
+        dfree(A->d_scols);
+        if (st == FS_E_OOM) clear_error();
+        return st == FS_E_OOM ? FS_OK : st;
+    }
+    FS_HIP_TRY(hipMemcpyAsync(A->d_sgrp, grp.data(), sizeof(StageGroup) * ng,
+                              hipMemcpyHostToDevice, s));
+    FS_HIP_TRY(launch_stage_lists(A->d_groups, A->n_groups, A->host.vec,
+                                  A->d_col, A->d_gbase, A->d_sgrp, A->d_lpat,
+                                  A->d_loc, A->d_scols, s));
+    FS_HIP_TRY(hipStreamSynchronize(s));
+    A->stage_max = std::max(most, 1);
+    if (A->d_jpos) {
+        // the value refresh reads row starts: the inverse map has served,
+        // and is larger than what was added here
+        dfree(A->d_imap);
+        bytes -= A->slots * int64_t(sizeof(int32_t));
+    }
+    acct += bytes;
     return FS_OK;
 }
 
@@ -197,6 +270,7 @@ fs_status create_from_host(int32_t n_rows, int32_t n_cols, int64_t nnz,
                                      sizeof(int32_t) * size_t(A->slots), s));
     FS_CREATE_HIP(launch_inverse_map(A->d_map, nnz, A->d_imap, s));
     if ((st = build_refresh_rows(A, h_rp, acct, s))) return fail(st);
+    if ((st = build_stage(A, acct, s))) return fail(st);
     if (n_rows) {
         FS_CREATE_HIP(hipMemcpyAsync(A->d_perm, L.perm.data(),
                                      sizeof(int32_t) * size_t(n_rows),
@@ -431,6 +505,7 @@ fs_status create_on_device(int32_t n_rows, int32_t n_cols, int64_t nnz,
                                   sizeof(int32_t) * size_t(A->slots), s));
     FS_DEV_HIP(launch_inverse_map(A->d_map, nnz, A->d_imap, s));
     if ((st = build_refresh_rows(A, h_rp.data(), acct, s))) return fail(st);
+    if ((st = build_stage(A, acct, s))) return fail(st);
     FS_DEV_HIP(launch_value_scatter(vals, A->d_map, nnz, A->d_val,
                                     A->d_val_f32, A->d_val_bf16, s));
     FS_DEV_HIP(hipStreamSynchronize(s));

@@ -182,6 +182,153 @@ __global__ __launch_bounds__(kBlock) void k_offsets16(
     }
 }
 
+// ------------------------------------------------------ staged products
+// Both kernels run one wavefront per workgroup and row group and find the
+// group's distinct columns with a bitmap over its column span in LDS.
+constexpr int kSpanNarrow = 65536;      // 16-bit offsets
+constexpr int kSpanWide = 320 * 1024;   // 40 KB of bitmap, 20 KB of counts
+
+// Smallest and largest column of the group (every lane), and their bitmap.
+// False when they span more than `span` columns.
+__device__ __forceinline__ bool column_bitmap(const int *__restrict__ cols,
+                                              int region, int lane, int span,
+                                              unsigned *bits, int &lo, int &hi)
+{
+    lo = INT_MAX;
+    hi = -1;
+    for (int t = lane; t < region; t += kWave) {
+        const int c = cols[t];
+        if (c >= 0) {
+            lo = min(lo, c);
+            hi = max(hi, c);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, __shfl_xor(lo, o, kWave));
+        hi = max(hi, __shfl_xor(hi, o, kWave));
+    }
+    if (hi < 0) {
+        lo = 0;
+        return true;
+    }
+    if (hi - lo >= span) return false;
+    for (int w = lane; w <= (hi - lo) >> 5; w += kWave) bits[w] = 0u;
+    __syncthreads();
+    for (int t = lane; t < region; t += kWave) {
+        const int c = cols[t];
+        if (c >= 0) atomicOr(bits + ((c - lo) >> 5), 1u << ((c - lo) & 31));
+    }
+    __syncthreads();
+    return true;
+}
+
+// Row patterns and distinct columns of a group.  Rows whose columns equal
+// the previous row's share its pattern, up to four rows per pattern (the
+// row tile of the multi-column products); lane j of a row of pattern p
+// reads position entry p * T + j.  counts[g] = {patterns, distinct columns
+// or -1}.
+__global__ __launch_bounds__(kWave) void k_stage_count(
+    const Group *__restrict__ groups, int V, const int *__restrict__ slot_col,
+    int span, uint8_t *__restrict__ lpat, int2 *__restrict__ counts)
+{
+    extern __shared__ unsigned bits[];
+    const int g = int(blockIdx.x), lane = int(threadIdx.x);
+    const Group G = load_group(gbl(groups), g);
+    const int *cols = slot_col + long(G.base64) * kWave;
+    const int width = G.width_lt & 0xffffff, lt = G.width_lt >> 24;
+    const int T = 1 << lt, row = lane >> lt;
+    int differs = row == 0;
+    for (int s = 0; s < width; ++s) {
+        const int c = cols[(s / V) * kWave * V + lane * V + s % V];
+        const int up = __shfl(c, lane >= T ? lane - T : lane, kWave);
+        differs |= c != up;
+    }
+    for (int o = 1; o < T; o <<= 1) differs |= __shfl_xor(differs, o, kWave);
+    const unsigned long long starts = __ballot(differs != 0);
+    // this row's pattern; lanes past the last row stay with its pattern
+    int p = -1, run = 0;
+    for (int r = 0; r <= min(row, G.nrows - 1); ++r) {
+        if (((starts >> (r << lt)) & 1) || run == 4) {
+            ++p;
+            run = 0;
+        }
+        ++run;
+    }
+    lpat[long(g) * kWave + lane] = uint8_t(p * T + (lane & (T - 1)));
+    int lo, hi, nd = 0;
+    if (!column_bitmap(cols, width * kWave, lane, span, bits, lo, hi)) {
+        nd = -1;
+    } else if (hi >= 0) {
+        for (int w = lane; w <= (hi - lo) >> 5; w += kWave) nd += __popc(bits[w]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) nd += __shfl_xor(nd, o, kWave);
+    }
+    if (lane == kWave - 1) counts[g] = make_int2(p + 1, nd);
+}
+
+// The group's column list (ascending) and every pattern's positions in it,
+// four slots per entry; padding slots, and slots past the width, hold the
+// list's length.
+template <typename E>
+__global__ __launch_bounds__(kWave) void k_stage_lists(
+    const Group *__restrict__ groups, int V, const int *__restrict__ slot_col,
+    int span, const int *__restrict__ gbase,
+    const StageGroup *__restrict__ grp, const uint8_t *__restrict__ lpat,
+    uint16_t *__restrict__ loc, E *__restrict__ list)
+{
+    extern __shared__ unsigned bits[];
+    uint16_t *before = reinterpret_cast<uint16_t *>(bits + span / 32);
+    const int g = int(blockIdx.x), lane = int(threadIdx.x);
+    const Group G = load_group(gbl(groups), g);
+    const StageGroup sg = grp[g];
+    const int *cols = slot_col + long(G.base64) * kWave;
+    const int width = G.width_lt & 0xffffff, T = 1 << (G.width_lt >> 24);
+    int lo, hi;
+    // every span fits (k_stage_count)
+    column_bitmap(cols, width * kWave, lane, span, bits, lo, hi);
+    const int words = hi < 0 ? 0 : ((hi - lo) >> 5) + 1;
+    const int b0 = gbase ? gbase[g] : 0;
+    int done = 0;
+    for (int w0 = 0; w0 < words; w0 += kWave) {
+        const int w = w0 + lane;
+        unsigned m = w < words ? bits[w] : 0u;
+        int n = __popc(m), at = n;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int u = __shfl_up(at, o, kWave);
+            if (lane >= o) at += u;
+        }
+        at += done - n;                       // set bits before this word
+        done = __shfl(at + n, kWave - 1, kWave);
+        if (w < words) before[w] = uint16_t(at);
+        for (; m; m &= m - 1)
+            list[sg.list + at++] = E(lo + 32 * w + __ffs(m) - 1 - b0);
+    }
+    __syncthreads();
+    const int me = lpat[long(g) * kWave + lane];
+    const bool first =
+        lane < T || lpat[long(g) * kWave + (lane >= T ? lane - T : 0)] != me;
+    if (!first) return;
+    for (int j = 0; j < (width + 3) / 4; ++j) {
+        ushort4 o;
+        uint16_t *const po = &o.x;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int s = 4 * j + t;
+            const int c =
+                s < width ? cols[(s / V) * kWave * V + lane * V + s % V] : -1;
+            int at = sg.nd;
+            if (c >= 0) {
+                const int w = (c - lo) >> 5;
+                at = before[w] + __popc(bits[w] & ((1u << ((c - lo) & 31)) - 1u));
+            }
+            po[t] = uint16_t(at);
+        }
+        reinterpret_cast<ushort4 *>(loc)[sg.loc + long(j) * sg.per + me] = o;
+    }
+}
+
 // Inverse of the CSR-position -> slot map: imap[map[k]] = k (padding slots
 // keep the -1 they were filled with).
 __global__ __launch_bounds__(kBlock) void k_inverse_map(
@@ -407,6 +554,39 @@ hipError_t launch_assign_slots(const Group *groups, int32_t ngroups,
     hipLaunchKernelGGL(k_assign_slots, dim3(wave_grid(ngroups)), dim3(kBlock),
                        0, s, groups, ngroups, vec, perm, iperm, rowptr, col,
                        slot_col, map, lohi, dup);
+    return hipGetLastError();
+}
+
+hipError_t launch_stage_count(const Group *groups, int32_t ngroups,
+                              int32_t vec, const int32_t *slot_col,
+                              bool narrow, uint8_t *lpat, int2 *counts,
+                              hipStream_t s)
+{
+    if (ngroups == 0) return hipSuccess;
+    const int span = narrow ? kSpanNarrow : kSpanWide;
+    hipLaunchKernelGGL(k_stage_count, dim3(ngroups), dim3(kWave), span / 8, s,
+                       groups, vec, slot_col, span, lpat, counts);
+    return hipGetLastError();
+}
+
+hipError_t launch_stage_lists(const Group *groups, int32_t ngroups,
+                              int32_t vec, const int32_t *slot_col,
+                              const int32_t *gbase, const StageGroup *grp,
+                              const uint8_t *lpat, uint16_t *loc, void *cols,
+                              hipStream_t s)
+{
+    if (ngroups == 0) return hipSuccess;
+    const int span = gbase ? kSpanNarrow : kSpanWide;
+    const size_t lds = size_t(span / 32) * (sizeof(unsigned) + sizeof(uint16_t));
+    if (gbase)
+        hipLaunchKernelGGL(k_stage_lists<uint16_t>, dim3(ngroups),
+                           dim3(kWave), lds, s, groups, vec, slot_col, span,
+                           gbase, grp, lpat, loc,
+                           static_cast<uint16_t *>(cols));
+    else
+        hipLaunchKernelGGL(k_stage_lists<int32_t>, dim3(ngroups), dim3(kWave),
+                           lds, s, groups, vec, slot_col, span, gbase, grp,
+                           lpat, loc, static_cast<int32_t *>(cols));
     return hipGetLastError();
 }
 

@@ -15,6 +15,7 @@ typedef double dv2 __attribute__((ext_vector_type(2)));
 typedef int iv2 __attribute__((ext_vector_type(2)));
 typedef float fv2 __attribute__((ext_vector_type(2)));
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+typedef unsigned short us4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWavesPerBlock = kBlock / kWave;
 
@@ -280,6 +281,190 @@ __device__ __forceinline__ Group load_group(gptr<Group> groups, int g)
 __device__ __forceinline__ int load_gbase(gptr<int32_t> gbase, int g)
 {
     return gbase ? __builtin_amdgcn_readfirstlane(gbase[g]) : 0;
+}
+
+template <typename VT, int V> struct Pack;
+template <> struct Pack<double, 1> { typedef double T; };
+template <> struct Pack<double, 2> { typedef dv2 T; };
+template <> struct Pack<float, 1> { typedef float T; };
+template <> struct Pack<float, 2> { typedef fv2 T; };
+template <> struct Pack<uint16_t, 1> { typedef uint16_t T; };
+template <> struct Pack<uint16_t, 2> { typedef us2 T; };
+
+template <typename ST> __device__ __forceinline__ ST widen(double v) { return ST(v); }
+template <typename ST> __device__ __forceinline__ ST widen(float v) { return ST(v); }
+template <typename ST> __device__ __forceinline__ ST widen(uint16_t h)
+{
+    return ST(__uint_as_float(uint32_t(h) << 16));
+}
+
+template <typename VT, typename ST, int V>
+__device__ __forceinline__ void unpack(typename Pack<VT, V>::T a, ST (&o)[V])
+{
+    if constexpr (V == 1) {
+        o[0] = widen<ST>(a);
+    } else {
+        o[0] = widen<ST>(a.x);
+        o[1] = widen<ST>(a.y);
+    }
+}
+
+// Order this wavefront's LDS writes before its later LDS reads (and its
+// reads before later writes): LDS operations of one wavefront execute in
+// order, so only the compiler has to be kept from moving them.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// This wavefront's staging buffer in the block's dynamic LDS: `stage` + 1
+// entries per wavefront.
+template <typename ST> __device__ __forceinline__ ST *stage_buffer(int stage)
+{
+    extern __shared__ double stage_lds_[];
+    return reinterpret_cast<ST *>(stage_lds_) +
+           __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)) * (stage + 1);
+}
+
+// This lane's share of its row, as group_lane_sum forms it (even slots and
+// odd slots apart, each in slot order: the same bits), with the entries of
+// x staged in LDS.  The slot loop then only streams -- values and 2-byte
+// positions, two batches in flight -- and reads LDS: a gather from global
+// memory waits behind the stream loads issued before it (the vector cache
+// returns in order), which cost the unstaged loop 13-16% of its time on
+// the elasticity matrices, and their rows' three-fold repeated gathers go
+// with it.  The first batch is requested before the staging.
+template <typename VT, typename ST, int V, bool NARROW>
+__device__ __forceinline__ ST staged_lane_sum(const Group &g, int gi, int lane,
+                                              gptr<VT> val,
+                                              const StageArgs &a, gptr<ST> x,
+                                              ST *xs)
+{
+    typedef typename Pack<VT, V>::T PV;
+    // slots per batch: 16 halve the loads' latency share for 2-byte values
+    // (config-1 matrix, us: bf16 23.4 with 8, 22.0 with 16; float 32.7 with
+    // 8, 37.1 with 16, whose registers leave 5 wavefronts per SIMD)
+    constexpr int B = sizeof(VT) == 2 ? 16 : 8;
+    constexpr int U = B / V, L = B / 4;
+    const auto gp = gbl(a.grp) + gi;
+    const int per = __builtin_amdgcn_readfirstlane(gp->per);
+    const int nd = __builtin_amdgcn_readfirstlane(gp->nd);
+    const long l0 = __builtin_amdgcn_readfirstlane(gp->list);
+    const gptr<us4> pl = reinterpret_cast<gptr<us4>>(gbl(a.loc)) +
+                         __builtin_amdgcn_readfirstlane(gp->loc);
+    const unsigned me =
+        per == kWave ? unsigned(lane) : gbl(a.lpat)[long(gi) * kWave + lane];
+    const int width = g.width_lt & 0xffffff;
+    const gptr<PV> pv =
+        reinterpret_cast<gptr<PV>>(val + long(g.base64) * kWave);
+    const int nb = (width + B - 1) / B, full = width / B;
+    auto load = [&](us4 (&c)[L], PV (&v)[U], int b) {
+        if (b < full) {
+#pragma unroll
+            for (int l = 0; l < L; ++l) c[l] = (pl + long(b * L + l) * per)[me];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                v[u] = __builtin_nontemporal_load(pv + (b * U + u) * kWave + lane);
+        } else {
+#pragma unroll
+            for (int l = 0; l < L; ++l)
+                if (b * B + 4 * l < width) c[l] = (pl + long(b * L + l) * per)[me];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if ((b * U + u) * V < width)
+                    v[u] = __builtin_nontemporal_load(pv + (b * U + u) * kWave +
+                                                      lane);
+        }
+    };
+    ST acc0 = ST(0), acc1 = ST(0);
+    auto use = [&](const us4 (&c)[L], const PV (&v)[U], int b) {
+        auto slots = [&](auto all) {
+            ST xv[B];
+#pragma unroll
+            for (int i = 0; i < B; ++i)
+                if (decltype(all)::value || b * B + i < width)
+                    xv[i] = xs[c[i / 4][i % 4]];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (!decltype(all)::value && (b * U + u) * V >= width) continue;
+                ST av[V];
+                unpack<VT, ST, V>(v[u], av);
+#pragma unroll
+                for (int t = 0; t < V; ++t) {
+                    ST &acc = ((u * V + t) & 1) ? acc1 : acc0;
+                    acc = fma(av[t], xv[u * V + t], acc);
+                }
+            }
+        };
+        if (b < full) slots(std::true_type());
+        else slots(std::false_type());
+    };
+    us4 c0[L], c1[L];
+    PV v0[U], v1[U];
+    if (nb > 0) load(c0, v0, 0);
+    // x of the listed columns, up to eight gathers in flight per lane; the
+    // entry after the last is the zero that padding slots read
+    wave_lds_sync();
+    constexpr int S = 8;
+    for (int i0 = 0; i0 < nd; i0 += S * kWave) {
+        int c[S];
+        ST v[S];
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+            if (i0 + u * kWave < nd) {
+                const int i = min(i0 + u * kWave + lane, nd - 1);
+                if constexpr (NARROW)
+                    c[u] = static_cast<gptr<uint16_t>>(gbl(a.cols))[l0 + i];
+                else
+                    c[u] = static_cast<gptr<int32_t>>(gbl(a.cols))[l0 + i];
+            }
+        const int gb = NARROW ? load_gbase(gbl(a.gbase), gi) : 0;
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+            if (i0 + u * kWave < nd) v[u] = x[gb + c[u]];
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+            if (i0 + u * kWave + lane < nd) xs[i0 + u * kWave + lane] = v[u];
+    }
+    if (lane == 0) xs[nd] = ST(0);
+    wave_lds_sync();
+    for (int b = 0; b < nb; b += 2) {
+        if (b + 1 < nb) load(c1, v1, b + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        use(c0, v0, b);
+        if (b + 1 >= nb) break;
+        if (b + 2 < nb) load(c0, v0, b + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        use(c1, v1, b + 1);
+    }
+    return acc0 + acc1;
+}
+
+// y[row or yperm[row]] = (A x)[row], staged: one row group per wavefront.
+template <typename VT, typename ST, int V, bool SCATTER, bool NARROW>
+__global__ __launch_bounds__(kBlock) void k_spmv_staged(
+    const Group *__restrict__ groups, int ngroups, const VT *__restrict__ val,
+    const StageArgs st, int stage, const ST *__restrict__ x,
+    ST *__restrict__ y, const int *__restrict__ yperm)
+{
+    const int b = xcd_remap(blockIdx.x, gridDim.x);
+    const int g = __builtin_amdgcn_readfirstlane(
+        b * kWavesPerBlock + int(threadIdx.x >> 6));
+    if (g >= ngroups) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const Group gd = load_group(gbl(groups), g);
+    const int lt = gd.width_lt >> 24;
+    const ST acc = row_reduce(
+        staged_lane_sum<VT, ST, V, NARROW>(gd, g, lane, gbl(val), st, gbl(x),
+                                           stage_buffer<ST>(stage)),
+        lt);
+    const int r = lane >> lt;
+    if ((lane & ((1 << lt) - 1)) == 0 && r < gd.nrows) {
+        const int row = gd.row0 + r;
+        y[SCATTER ? yperm[row] : row] = acc;
+    }
 }
 
 // float -> bfloat16, round to nearest even; NaN stays a (quiet) NaN.

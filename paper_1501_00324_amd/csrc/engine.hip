@@ -45,32 +45,6 @@ namespace {
 // wavefront loses ~20% to tail imbalance (measured on config 1).
 constexpr int kMaxSpmvBlocks = 16384;
 
-template <typename VT, int V> struct Pack;
-template <> struct Pack<double, 1> { typedef double T; };
-template <> struct Pack<double, 2> { typedef dv2 T; };
-template <> struct Pack<float, 1> { typedef float T; };
-template <> struct Pack<float, 2> { typedef fv2 T; };
-template <> struct Pack<uint16_t, 1> { typedef uint16_t T; };
-template <> struct Pack<uint16_t, 2> { typedef us2 T; };
-
-template <typename ST> __device__ __forceinline__ ST widen(double v) { return ST(v); }
-template <typename ST> __device__ __forceinline__ ST widen(float v) { return ST(v); }
-template <typename ST> __device__ __forceinline__ ST widen(uint16_t h)
-{
-    return ST(__uint_as_float(uint32_t(h) << 16));
-}
-
-template <typename VT, typename ST, int V>
-__device__ __forceinline__ void unpack(typename Pack<VT, V>::T a, ST (&o)[V])
-{
-    if constexpr (V == 1) {
-        o[0] = widen<ST>(a);
-    } else {
-        o[0] = widen<ST>(a.x);
-        o[1] = widen<ST>(a.y);
-    }
-}
-
 // acc{0,1}[c] += a * X[col, c] over this lane's slots, even slots into
 // acc0, odd slots into acc1.  Padded slots (col -1) read row 0 of X and
 // drop the product through a select.
@@ -246,16 +220,6 @@ template <typename ST, int V> __device__ __forceinline__ SlotRec<ST> *coop_buffe
 {
     __shared__ SlotRec<ST> recs[kWavesPerBlock * 2 * V * kWave];
     return recs;
-}
-
-// Order this wavefront's LDS writes before its later LDS reads (and its
-// reads before later writes): LDS operations of one wavefront execute in
-// order, so only the compiler has to be kept from moving them.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Multi-column product of one row group with cooperative gathers (KM > 1).
@@ -537,15 +501,15 @@ __device__ __forceinline__ void coop_group_pair(const Group &g, int lane,
 // product spills a register and the solve slows by 13%), KM = 8 and 16
 // hold 4 (128 registers), except the float KM = 16 product, which needs
 // more registers and keeps 3.
-constexpr int spmm_dot_min_waves(int km, int st_bytes)
+constexpr int spmm_dot_min_waves(int km, int st_bytes, bool staged)
 {
-    return km == 16 && st_bytes == 4 ? 3 : km >= 8 ? 4 : km == 1 ? 7 : 1;
+    return staged ? 1 : km == 16 && st_bytes == 4 ? 3 : km >= 8 ? 4 : km == 1 ? 7 : 1;
 }
 
 // Q = A P for every column with per-block partials of p_c . q_c.
-template <typename VT, typename ST, int V, int KM>
-__global__ __launch_bounds__(kBlock, spmm_dot_min_waves(KM, int(sizeof(ST)))) void k_spmm_dot(
-    const SysDesc *__restrict__ sys, const int *__restrict__ smap)
+template <typename VT, typename ST, int V, int KM, bool STG>
+__global__ __launch_bounds__(kBlock, spmm_dot_min_waves(KM, int(sizeof(ST)), STG)) void k_spmm_dot(
+    const SysDesc *__restrict__ sys, const int *__restrict__ smap, int stage)
 {
     const int gb = xcd_remap(blockIdx.x, gridDim.x);
     const SysDesc &S = sys[smap[gb]];
@@ -570,10 +534,17 @@ __global__ __launch_bounds__(kBlock, spmm_dot_min_waves(KM, int(sizeof(ST)))) vo
                 const bool own = (lane & ((1 << lt) - 1)) == 0 && r < gd.nrows;
                 const long row = gd.row0 + (r < gd.nrows ? r : 0);
                 const ST pr = P[row];          // early, off the tail
-                ST a0[1] = {ST(0)}, a1[1] = {ST(0)};
-                lane_sums<VT, ST, V, 1, N>(gd, lane, val, cst, gb, P, 1, 1,
-                                           a0, a1);
-                const ST v = row_reduce(a0[0] + a1[0], lt);
+                ST a;
+                if constexpr (STG) {
+                    a = staged_lane_sum<VT, ST, V, N>(gd, g, lane, val, S.st,
+                                                      P, stage_buffer<ST>(stage));
+                } else {
+                    ST a0[1] = {ST(0)}, a1[1] = {ST(0)};
+                    lane_sums<VT, ST, V, 1, N>(gd, lane, val, cst, gb, P, 1,
+                                               1, a0, a1);
+                    a = a0[0] + a1[0];
+                }
+                const ST v = row_reduce(a, lt);
                 if (own) {
                     Q[row] = v;
                     dot[0] += double(pr) * double(v);
@@ -866,9 +837,9 @@ __global__ __launch_bounds__(kBlock) void k_pupdate(
 // on a new right-hand side b (as MODE 1, and the tolerance becomes
 // rtol |b_new|): the search direction is kept, so a refinement step
 // continues the Krylov iteration instead of restarting it.
-template <typename VT, typename ST, int V, int KM, bool XZ, int MODE>
+template <typename VT, typename ST, int V, int KM, bool XZ, int MODE, bool STG>
 __global__ __launch_bounds__(kBlock) void k_residual(
-    const SysDesc *__restrict__ sys, const int *__restrict__ smap)
+    const SysDesc *__restrict__ sys, const int *__restrict__ smap, int stage)
 {
     const int gb = xcd_remap(blockIdx.x, gridDim.x);
     const SysDesc &S = sys[smap[gb]];
@@ -899,7 +870,13 @@ __global__ __launch_bounds__(kBlock) void k_residual(
 #pragma unroll
         for (int c = 0; c < KM; ++c) a0[c] = a1[c] = ST(0);
         if (!XZ) {
-            if (S.gbase)
+            if constexpr (STG) {
+                ST *const xs = stage_buffer<ST>(stage);
+                a0[0] = S.gbase ? staged_lane_sum<VT, ST, V, true>(
+                                      gd, g, lane, val, S.st, X, xs)
+                                : staged_lane_sum<VT, ST, V, false>(
+                                      gd, g, lane, val, S.st, X, xs);
+            } else if (S.gbase)
                 lane_sums<VT, ST, V, KM, true>(gd, lane, val, cst,
                                                load_gbase(gbl(S.gbase), g), X,
                                                k, k, a0, a1);
@@ -1109,6 +1086,21 @@ int32_t engine_vec_blocks(int32_t n, int32_t k)
     return k == 1 ? std::min(b, 512) : b;
 }
 
+// f(true_type) when the launch's single-column products are staged.
+template <int KM, class F> static void with_stage(const EngineLaunch &L, F &&f)
+{
+    if constexpr (KM == 1) {
+        if (L.stage) return f(std::true_type());
+    }
+    f(std::false_type());
+}
+
+// LDS of a staged launch.
+template <typename ST> static size_t stage_lds(const EngineLaunch &L)
+{
+    return sizeof(ST) * size_t(L.stage + 1) * kWavesPerBlock;
+}
+
 hipError_t engine_iteration(const EngineLaunch &L, hipStream_t s)
 {
     with_types(L.vt, L.st, [&](auto tt) {
@@ -1116,12 +1108,18 @@ hipError_t engine_iteration(const EngineLaunch &L, hipStream_t s)
         typedef typename decltype(tt)::S ST;
         with_km(L.km, [&](auto kt) {
             constexpr int KM = decltype(kt)::value;
-            if (L.vec == 1)
-                hipLaunchKernelGGL((k_spmm_dot<VT, ST, 1, KM>), dim3(L.sblocks),
-                                   dim3(kBlock), 0, s, L.sys, L.smap);
-            else
-                hipLaunchKernelGGL((k_spmm_dot<VT, ST, 2, KM>), dim3(L.sblocks),
-                                   dim3(kBlock), 0, s, L.sys, L.smap);
+            with_stage<KM>(L, [&](auto sg) {
+                constexpr bool STG = decltype(sg)::value;
+                const size_t lds = STG ? stage_lds<ST>(L) : 0;
+                if (L.vec == 1)
+                    hipLaunchKernelGGL((k_spmm_dot<VT, ST, 1, KM, STG>),
+                                       dim3(L.sblocks), dim3(kBlock), lds, s,
+                                       L.sys, L.smap, L.stage);
+                else
+                    hipLaunchKernelGGL((k_spmm_dot<VT, ST, 2, KM, STG>),
+                                       dim3(L.sblocks), dim3(kBlock), lds, s,
+                                       L.sys, L.smap, L.stage);
+            });
             if constexpr (KM == 1) {
                 hipLaunchKernelGGL((k_update_fused<ST>), dim3(L.vblocks),
                                    dim3(kBlock), 0, s, L.sys, L.vmap);
@@ -1142,26 +1140,27 @@ hipError_t engine_iteration(const EngineLaunch &L, hipStream_t s)
     return hipGetLastError();
 }
 
-template <typename VT, typename ST, int V, int KM, bool XZ>
-static void residual_mode(const EngineLaunch &L, int mode, hipStream_t s)
+template <typename VT, typename ST, int V, int KM, bool XZ, int MODE>
+static void residual_mode(const EngineLaunch &L, hipStream_t s)
 {
     const dim3 g(L.sblocks), b(kBlock), f(L.ncols);
-    if (mode == 0) {
-        hipLaunchKernelGGL((k_residual<VT, ST, V, KM, XZ, 0>), g, b, 0, s,
-                           L.sys, L.smap);
-        hipLaunchKernelGGL(k_fin_residual<0>, f, b, 0, s, L.sys, L.cmap);
-    } else if (mode == 1) {
-        hipLaunchKernelGGL((k_residual<VT, ST, V, KM, XZ, 1>), g, b, 0, s,
-                           L.sys, L.smap);
-        hipLaunchKernelGGL(k_fin_residual<1>, f, b, 0, s, L.sys, L.cmap);
-    } else if (mode == 2) {
-        hipLaunchKernelGGL((k_residual<VT, ST, V, KM, XZ, 2>), g, b, 0, s,
-                           L.sys, L.smap);
-        hipLaunchKernelGGL(k_fin_residual<2>, f, b, 0, s, L.sys, L.cmap);
-    } else {
-        hipLaunchKernelGGL((k_residual<VT, ST, V, KM, XZ, 3>), g, b, 0, s,
-                           L.sys, L.smap);
-        hipLaunchKernelGGL(k_fin_residual<3>, f, b, 0, s, L.sys, L.cmap);
+    with_stage<XZ ? 0 : KM>(L, [&](auto sg) {
+        constexpr bool STG = decltype(sg)::value;
+        hipLaunchKernelGGL((k_residual<VT, ST, V, KM, XZ, MODE, STG>), g, b,
+                           STG ? stage_lds<ST>(L) : 0, s, L.sys, L.smap,
+                           L.stage);
+    });
+    hipLaunchKernelGGL(k_fin_residual<MODE>, f, b, 0, s, L.sys, L.cmap);
+}
+
+template <typename VT, typename ST, int V, int KM, bool XZ>
+static void residual_modes(const EngineLaunch &L, int mode, hipStream_t s)
+{
+    switch (mode) {
+    case 0: residual_mode<VT, ST, V, KM, XZ, 0>(L, s); break;
+    case 1: residual_mode<VT, ST, V, KM, XZ, 1>(L, s); break;
+    case 2: residual_mode<VT, ST, V, KM, XZ, 2>(L, s); break;
+    default: residual_mode<VT, ST, V, KM, XZ, 3>(L, s); break;
     }
 }
 
@@ -1174,11 +1173,11 @@ hipError_t engine_residual(const EngineLaunch &L, int32_t mode, bool x_zero,
         with_km(L.km, [&](auto kt) {
             constexpr int KM = decltype(kt)::value;
             if (L.vec == 1) {
-                if (x_zero) residual_mode<VT, ST, 1, KM, true>(L, mode, s);
-                else residual_mode<VT, ST, 1, KM, false>(L, mode, s);
+                if (x_zero) residual_modes<VT, ST, 1, KM, true>(L, mode, s);
+                else residual_modes<VT, ST, 1, KM, false>(L, mode, s);
             } else {
-                if (x_zero) residual_mode<VT, ST, 2, KM, true>(L, mode, s);
-                else residual_mode<VT, ST, 2, KM, false>(L, mode, s);
+                if (x_zero) residual_modes<VT, ST, 2, KM, true>(L, mode, s);
+                else residual_modes<VT, ST, 2, KM, false>(L, mode, s);
             }
         });
     });
@@ -1489,6 +1488,21 @@ hipError_t launch_spmv_lowp(const fs_csr *A, int32_t dtype, const float *x,
         const VT *val = dtype == FS_DT_F32
                             ? reinterpret_cast<const VT *>(A->d_val_f32)
                             : reinterpret_cast<const VT *>(A->d_val_bf16);
+        if (A->d_sgrp) {
+            const size_t lds =
+                sizeof(float) * size_t(A->stage_max + 1) * kWavesPerBlock;
+            if (A->d_gbase)
+                hipLaunchKernelGGL((k_spmv_staged<VT, float, V, false, true>),
+                                   grid, dim3(kBlock), lds, s, A->d_groups,
+                                   A->n_groups, val, stage_of(A),
+                                   A->stage_max, x, y, nullptr);
+            else
+                hipLaunchKernelGGL((k_spmv_staged<VT, float, V, false, false>),
+                                   grid, dim3(kBlock), lds, s, A->d_groups,
+                                   A->n_groups, val, stage_of(A),
+                                   A->stage_max, x, y, nullptr);
+            return;
+        }
         if (A->d_col16)
             hipLaunchKernelGGL((k_spmm<VT, float, V, 1, false, true>), grid,
                                dim3(kBlock), 0, s, A->d_groups, A->n_groups,

@@ -78,6 +78,32 @@ fs_status layout_groups(int32_t n_rows, int32_t n_cols, const int32_t *rowptr,
                         const fs_csr_opts &o, const LayoutParams &prm,
                         HostLayout &L);
 
+// ------------------------------------------------------- staged products
+// Single-column products whose wavefronts first copy the entries of x that
+// their row group needs into LDS (build.hip builds the arrays; device.h:
+// staged_lane_sum).  The group's distinct columns are listed once, in
+// ascending order, and every slot holds the position of its column in that
+// list (the list's length marks padding).  Rows of a group with the same
+// columns -- the unknowns of one mesh node -- form a pattern and share one
+// copy of their positions; four slots of a lane are stored together.
+struct StageGroup {
+    int32_t loc;             // first position entry (of four slots)
+    int32_t per;             // entries per four slots: patterns * lanes per row
+    int32_t list;            // first entry of the column list
+    int32_t nd;              // distinct columns
+};
+struct StageArgs {
+    const StageGroup *grp;   // NULL: not staged
+    const uint16_t *loc;     // positions, four per entry
+    const uint8_t *lpat;     // 64 per group: each lane's entry (per < 64)
+    const void *cols;        // column lists: 16-bit offsets from gbase, or
+    const int32_t *gbase;    //   (gbase NULL) 32-bit columns
+};
+// Most distinct columns of a group (40 KB of LDS per workgroup), and how
+// many of them per slot, over the matrix, the staging pays for.
+constexpr int32_t kStageMax = 1280;
+constexpr double kStageMost = 0.45;
+
 // ------------------------------------------------- batched CG engine state
 // Status of one right-hand side.
 enum { CG_RUNNING = 0, CG_CONVERGED = 1, CG_RECURRENCE_MET = 2,
@@ -101,6 +127,7 @@ struct SysDesc {
     const int32_t *col;          // 32-bit slot columns
     const void *cstream;         // column stream of the products: col, or
     const int32_t *gbase;        //   16-bit offsets from gbase[group]
+    StageArgs st;                // single-column products (st.grp NULL: off)
     int32_t n, ngroups, k, maxit;
     int32_t sb0, snb;            // blocks in the group-shaped grid
     int32_t vb0, vnb;            // blocks in the row-shaped grid
@@ -139,6 +166,9 @@ struct EngineLaunch {            // one batched launch shape
     const int32_t *vmap;         // row-shaped grid block -> system
     const int2 *cmap;            // finalize block -> (system, column)
     int32_t sblocks, vblocks, ncols;  // grid sizes
+    int32_t stage;               // distinct columns of the widest group when
+                                 //   every system is staged, else 0 (both
+                                 //   products form the same bits)
 };
 
 int32_t engine_spmv_blocks(int32_t ngroups);
@@ -268,6 +298,12 @@ struct fs_csr {
     int32_t *d_col = nullptr;
     uint16_t *d_col16 = nullptr;   // 16-bit offsets (index_bits 16), or NULL
     int32_t *d_gbase = nullptr;    // per-group column base for d_col16
+    // staged products (NULL: off) and their widest group
+    fs::StageGroup *d_sgrp = nullptr;
+    uint16_t *d_loc = nullptr;
+    uint8_t *d_lpat = nullptr;
+    void *d_scols = nullptr;
+    int32_t stage_max = 0;
     int32_t *d_map = nullptr;
     int32_t *d_imap = nullptr;     // slot -> CSR position, -1 = padding
     // the product runs the pipelined lane sum: lanes own 32 or more slots
@@ -308,6 +344,11 @@ struct fs_csr {
 };
 
 namespace fs {
+inline StageArgs stage_of(const fs_csr *A)
+{
+    return {A->d_sgrp, A->d_loc, A->d_lpat, A->d_scols, A->d_gbase};
+}
+
 // ---------------------------------------------------------------- launchers
 // All launchers are asynchronous on stream s and return hipError_t.
 hipError_t launch_value_scatter(const double *vals, const int32_t *map,
@@ -345,6 +386,18 @@ hipError_t launch_assign_slots(const Group *groups, int32_t ngroups,
 hipError_t launch_offsets16(const Group *groups, int32_t ngroups,
                             const int32_t *slot_col, const int2 *lohi,
                             uint16_t *col16, int32_t *gbase, hipStream_t s);
+// Staged products: per group the row patterns (lpat, their number) and the
+// number of distinct columns (-1: they span too far), then with grp set the
+// column lists and positions.
+hipError_t launch_stage_count(const Group *groups, int32_t ngroups,
+                              int32_t vec, const int32_t *slot_col,
+                              bool narrow, uint8_t *lpat, int2 *counts,
+                              hipStream_t s);
+hipError_t launch_stage_lists(const Group *groups, int32_t ngroups,
+                              int32_t vec, const int32_t *slot_col,
+                              const int32_t *gbase, const StageGroup *grp,
+                              const uint8_t *lpat, uint16_t *loc, void *cols,
+                              hipStream_t s);
 hipError_t launch_gather(int32_t n, const int32_t *perm, const double *in,
                          double *out, hipStream_t s);
 hipError_t launch_scatter(int32_t n, const int32_t *perm, const double *in,

@@ -194,7 +194,8 @@ fs_status batch_build(Batch &B, hipStream_t s, bool async_upload)
     std::vector<SysDesc> descs(static_cast<size_t>(m));
     std::vector<int32_t> smap, vmap;
     B.cols.clear();
-    int32_t kmax = 1, sb = 0, vb = 0;
+    int32_t kmax = 1, sb = 0, vb = 0, stage = 0;
+    bool all_staged = true;
     for (int32_t i = 0; i < m; ++i) {
         CgSys &S = *B.members[size_t(i)];
         const fs_csr *A = S.A;
@@ -206,6 +207,9 @@ fs_status batch_build(Batch &B, hipStream_t s, bool async_upload)
         d.cstream = A->d_col16 ? static_cast<const void *>(A->d_col16)
                                : static_cast<const void *>(A->d_col);
         d.gbase = A->d_col16 ? A->d_gbase : nullptr;
+        d.st = stage_of(A);
+        all_staged &= A->stage_max > 0 || A->n_groups == 0;
+        stage = std::max(stage, A->stage_max);
         d.n = S.n;
         d.ngroups = A->n_groups;
         d.k = S.k;
@@ -310,6 +314,7 @@ fs_status batch_build(Batch &B, hipStream_t s, bool async_upload)
     B.L.sblocks = sb;
     B.L.vblocks = vb;
     B.L.ncols = nc;
+    B.L.stage = all_staged ? stage : 0;
     if (B.graph) (void)hipGraphExecDestroy(B.graph);
     B.graph = nullptr;
     B.graph_iters = 0;
