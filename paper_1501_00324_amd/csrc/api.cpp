@@ -171,6 +171,7 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
                                   A->d_loc, A->d_scols, s));
     FS_HIP_TRY(hipStreamSynchronize(s));
     A->stage_max = std::max(most, 1);
+    A->stream_loc = 8 * loc > kLocCached;
     if (A->d_jpos) {
         // the value refresh reads row starts: the inverse map has served,
         // and is larger than what was added here

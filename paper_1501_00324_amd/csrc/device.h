@@ -336,7 +336,7 @@ template <typename ST> __device__ __forceinline__ ST *stage_buffer(int stage)
 // returns in order), which cost the unstaged loop 13-16% of its time on
 // the elasticity matrices, and their rows' three-fold repeated gathers go
 // with it.  The first batch is requested before the staging.
-template <typename VT, typename ST, int V, bool NARROW>
+template <typename VT, typename ST, int V, bool NARROW, bool STREAM = false>
 __device__ __forceinline__ ST staged_lane_sum(const Group &g, int gi, int lane,
                                               gptr<VT> val,
                                               const StageArgs &a, gptr<ST> x,
@@ -360,17 +360,22 @@ __device__ __forceinline__ ST staged_lane_sum(const Group &g, int gi, int lane,
     const gptr<PV> pv =
         reinterpret_cast<gptr<PV>>(val + long(g.base64) * kWave);
     const int nb = (width + B - 1) / B, full = width / B;
+    auto position = [&](int j) {
+        const auto p = pl + long(j) * per + me;
+        if constexpr (STREAM) return __builtin_nontemporal_load(p);
+        else return *p;
+    };
     auto load = [&](us4 (&c)[L], PV (&v)[U], int b) {
         if (b < full) {
 #pragma unroll
-            for (int l = 0; l < L; ++l) c[l] = (pl + long(b * L + l) * per)[me];
+            for (int l = 0; l < L; ++l) c[l] = position(b * L + l);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 v[u] = __builtin_nontemporal_load(pv + (b * U + u) * kWave + lane);
         } else {
 #pragma unroll
             for (int l = 0; l < L; ++l)
-                if (b * B + 4 * l < width) c[l] = (pl + long(b * L + l) * per)[me];
+                if (b * B + 4 * l < width) c[l] = position(b * L + l);
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if ((b * U + u) * V < width)
@@ -443,7 +448,8 @@ __device__ __forceinline__ ST staged_lane_sum(const Group &g, int gi, int lane,
 }
 
 // y[row or yperm[row]] = (A x)[row], staged: one row group per wavefront.
-template <typename VT, typename ST, int V, bool SCATTER, bool NARROW>
+template <typename VT, typename ST, int V, bool SCATTER, bool NARROW,
+          bool STREAM = false>
 __global__ __launch_bounds__(kBlock) void k_spmv_staged(
     const Group *__restrict__ groups, int ngroups, const VT *__restrict__ val,
     const StageArgs st, int stage, const ST *__restrict__ x,
@@ -457,8 +463,8 @@ __global__ __launch_bounds__(kBlock) void k_spmv_staged(
     const Group gd = load_group(gbl(groups), g);
     const int lt = gd.width_lt >> 24;
     const ST acc = row_reduce(
-        staged_lane_sum<VT, ST, V, NARROW>(gd, g, lane, gbl(val), st, gbl(x),
-                                           stage_buffer<ST>(stage)),
+        staged_lane_sum<VT, ST, V, NARROW, STREAM>(
+            gd, g, lane, gbl(val), st, gbl(x), stage_buffer<ST>(stage)),
         lt);
     const int r = lane >> lt;
     if ((lane & ((1 << lt) - 1)) == 0 && r < gd.nrows) {

@@ -103,6 +103,13 @@ struct StageArgs {
 // many of them per slot, over the matrix, the staging pays for.
 constexpr int32_t kStageMax = 1280;
 constexpr double kStageMost = 0.45;
+// Positions up to this size are read through the caches, where they stay
+// from one product to the next (256 MB last-level cache); the FP64 product
+// streams larger ones like the values.  Three matrices in turn, us, cached / streamed:
+// P1 elasticity 64^3 (24 MB) 53.9 / 55.9, Q1 Laplacian 100^3 (54 MB) 50.2 /
+// 52.1, P1 Laplacian 126^3 (62 MB) 76.8 / 70.6, Q1 elasticity 87^3 (110 MB)
+// 242 / 237.
+constexpr int64_t kLocCached = int64_t(56) << 20;
 
 // ------------------------------------------------- batched CG engine state
 // Status of one right-hand side.
@@ -304,6 +311,7 @@ struct fs_csr {
     uint8_t *d_lpat = nullptr;
     void *d_scols = nullptr;
     int32_t stage_max = 0;
+    bool stream_loc = false;       // positions too large for the caches
     int32_t *d_map = nullptr;
     int32_t *d_imap = nullptr;     // slot -> CSR position, -1 = padding
     // the product runs the pipelined lane sum: lanes own 32 or more slots

@@ -162,11 +162,16 @@ void spmv_go(const fs_csr *A, const double *x, double *y,
 {
     const void *col = N ? static_cast<const void *>(A->d_col16)
                         : static_cast<const void *>(A->d_col);
-    if (A->d_sgrp)
+    const size_t lds =
+        sizeof(double) * size_t(A->stage_max + 1) * kWavesPerBlock;
+    if (A->d_sgrp && A->stream_loc)
+        hipLaunchKernelGGL((k_spmv_staged<double, double, V, S, N, true>),
+                           dim3(spmv_blocks(A->n_groups)), dim3(kBlock), lds,
+                           s, A->d_groups, A->n_groups, A->d_val, stage_of(A),
+                           A->stage_max, x, y, yperm);
+    else if (A->d_sgrp)
         hipLaunchKernelGGL((k_spmv_staged<double, double, V, S, N>),
-                           dim3(spmv_blocks(A->n_groups)), dim3(kBlock),
-                           sizeof(double) * size_t(A->stage_max + 1) *
-                               kWavesPerBlock,
+                           dim3(spmv_blocks(A->n_groups)), dim3(kBlock), lds,
                            s, A->d_groups, A->n_groups, A->d_val, stage_of(A),
                            A->stage_max, x, y, yperm);
     else if (A->pipe_product)
