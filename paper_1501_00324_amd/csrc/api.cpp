@@ -136,7 +136,7 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
                               hipMemcpyDeviceToHost, s));
     FS_HIP_TRY(hipStreamSynchronize(s));
     std::vector<StageGroup> grp(ng);
-    int64_t loc = 0, list = 0;
+    int64_t loc = 0, list = 0, patterns = 0;
     int32_t most = 0;
     for (size_t g = 0; g < ng; ++g) {
         const int32_t wl = A->host.groups[g].width_lt;
@@ -146,6 +146,7 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
         grp[g] = StageGroup{int32_t(loc), per, int32_t(list), nd};
         loc += int64_t(per) * (((wl & 0xffffff) + 3) / 4);
         list += nd;
+        patterns += cnt[g].x;
     }
     if (most > kStageMax || double(list) > kStageMost * double(A->slots)) {
         dfree(A->d_lpat);
@@ -171,6 +172,7 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
                                   A->d_loc, A->d_scols, s));
     FS_HIP_TRY(hipStreamSynchronize(s));
     A->stage_max = std::max(most, 1);
+    A->row_tiles = double(A->n_rows) >= kTileRows * double(patterns);
     A->stream_loc = 8 * loc > kLocCached;
     if (A->d_jpos) {
         // the value refresh reads row starts: the inverse map has served,

@@ -12,6 +12,8 @@ namespace fs {
 namespace {
 
 typedef double dv2 __attribute__((ext_vector_type(2)));
+// a pair of doubles at any 8-byte address
+typedef double dv2u __attribute__((ext_vector_type(2), aligned(8)));
 typedef int iv2 __attribute__((ext_vector_type(2)));
 typedef float fv2 __attribute__((ext_vector_type(2)));
 typedef unsigned short us2 __attribute__((ext_vector_type(2)));

@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "device.h"
+#include "tiles.h"
 
 namespace fs {
 namespace {
@@ -503,10 +504,11 @@ __device__ __forceinline__ void coop_group_pair(const Group &g, int lane,
 // more registers and keeps 3.
 constexpr int spmm_dot_min_waves(int km, int st_bytes, bool staged)
 {
-    return staged ? 1 : km == 16 && st_bytes == 4 ? 3 : km >= 8 ? 4 : km == 1 ? 7 : 1;
+    return staged ? (km > 1 ? tile_waves(km) : 1) : km == 16 && st_bytes == 4 ? 3 : km >= 8 ? 4 : km == 1 ? 7 : 1;
 }
 
 // Q = A P for every column with per-block partials of p_c . q_c.
+// STG: one column, staged; KM > 1: on the matrix cores.
 template <typename VT, typename ST, int V, int KM, bool STG>
 __global__ __launch_bounds__(kBlock, spmm_dot_min_waves(KM, int(sizeof(ST)), STG)) void k_spmm_dot(
     const SysDesc *__restrict__ sys, const int *__restrict__ smap, int stage)
@@ -525,6 +527,25 @@ __global__ __launch_bounds__(kBlock, spmm_dot_min_waves(KM, int(sizeof(ST)), STG
     double dot[1] = {0.0};
     with_narrow(S.gbase != nullptr, [&](auto nt) {
         constexpr bool N = decltype(nt)::value;
+        if constexpr (STG && KM > 1) {
+            __shared__ TileBuf tiles[kWavesPerBlock];
+            constexpr int NP = tile_parts<KM>();
+            for (int i = g0 * NP + int(threadIdx.x >> 6); i < g1 * NP;
+                 i += kWavesPerBlock) {
+                const int g = __builtin_amdgcn_readfirstlane(i / NP);
+                const Group gd = load_group(gbl(S.groups), g);
+                tile_group<V, KM, N>(
+                    gd, g, lane, val, cst, N ? load_gbase(gbl(S.gbase), g) : 0,
+                    gbl(S.st.lpat), P, k, k, tiles[threadIdx.x >> 6],
+                    __builtin_amdgcn_readfirstlane(i % NP),
+                    [&](int rg, int q, double v) {
+                        const long e = long(gd.row0 + rg) * k + q;
+                        Q[e] = v;
+                        dot[0] += P[e] * v;
+                    });
+            }
+            return;
+        }
         for (int g = g0 + int(threadIdx.x >> 6); g < g1; g += kWavesPerBlock) {
             const Group gd =
                 load_group(gbl(S.groups), __builtin_amdgcn_readfirstlane(g));
@@ -1086,11 +1107,16 @@ int32_t engine_vec_blocks(int32_t n, int32_t k)
     return k == 1 ? std::min(b, 512) : b;
 }
 
-// f(true_type) when the launch's single-column products are staged.
-template <int KM, class F> static void with_stage(const EngineLaunch &L, F &&f)
+// f(true_type) when the launch's products are staged (one column) or run on
+// the matrix cores (4 or more columns, FP64).
+template <typename ST, int KM, class F>
+static void with_stage(const EngineLaunch &L, F &&f)
 {
     if constexpr (KM == 1) {
         if (L.stage) return f(std::true_type());
+    }
+    if constexpr (KM >= 4 && std::is_same<ST, double>::value) {
+        if (L.tiles) return f(std::true_type());
     }
     f(std::false_type());
 }
@@ -1108,9 +1134,9 @@ hipError_t engine_iteration(const EngineLaunch &L, hipStream_t s)
         typedef typename decltype(tt)::S ST;
         with_km(L.km, [&](auto kt) {
             constexpr int KM = decltype(kt)::value;
-            with_stage<KM>(L, [&](auto sg) {
+            with_stage<ST, KM>(L, [&](auto sg) {
                 constexpr bool STG = decltype(sg)::value;
-                const size_t lds = STG ? stage_lds<ST>(L) : 0;
+                const size_t lds = STG && KM == 1 ? stage_lds<ST>(L) : 0;
                 if (L.vec == 1)
                     hipLaunchKernelGGL((k_spmm_dot<VT, ST, 1, KM, STG>),
                                        dim3(L.sblocks), dim3(kBlock), lds, s,
@@ -1144,7 +1170,7 @@ template <typename VT, typename ST, int V, int KM, bool XZ, int MODE>
 static void residual_mode(const EngineLaunch &L, hipStream_t s)
 {
     const dim3 g(L.sblocks), b(kBlock), f(L.ncols);
-    with_stage<XZ ? 0 : KM>(L, [&](auto sg) {
+    with_stage<ST, (XZ || KM > 1) ? 0 : KM>(L, [&](auto sg) {
         constexpr bool STG = decltype(sg)::value;
         hipLaunchKernelGGL((k_residual<VT, ST, V, KM, XZ, MODE, STG>), g, b,
                            STG ? stage_lds<ST>(L) : 0, s, L.sys, L.smap,
@@ -1449,6 +1475,8 @@ hipError_t launch_spmm_f64(const fs_csr *A, int32_t k, const double *X,
     if (A->n_groups == 0) return hipSuccess;
     const dim3 grid((A->n_groups + kWavesPerBlock - 1) / kWavesPerBlock);
     const int km = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
+    if (A->row_tiles && km >= 4 && tile_fits(A->n_cols, ldx))
+        return launch_spmm_tiles(A, k, X, ldx, Y, ldy, yperm, s);
     with_km(km, [&](auto kt) {
         constexpr int KM = decltype(kt)::value;
         auto go = [&](auto vtag, auto stag) {

@@ -103,6 +103,9 @@ struct StageArgs {
 // many of them per slot, over the matrix, the staging pays for.
 constexpr int32_t kStageMax = 1280;
 constexpr double kStageMost = 0.45;
+// Rows per pattern, over the matrix, from which the multi-column products run
+// on the matrix cores (a pattern is a tile of up to four rows).
+constexpr double kTileRows = 2.0;
 // Positions up to this size are read through the caches, where they stay
 // from one product to the next (256 MB last-level cache); the FP64 product
 // streams larger ones like the values.  Three matrices in turn, us, cached / streamed:
@@ -173,6 +176,8 @@ struct EngineLaunch {            // one batched launch shape
     const int32_t *vmap;         // row-shaped grid block -> system
     const int2 *cmap;            // finalize block -> (system, column)
     int32_t sblocks, vblocks, ncols;  // grid sizes
+    int32_t tiles;               // 1: every system's rows share columns in
+                                 //   runs (matrix-core products)
     int32_t stage;               // distinct columns of the widest group when
                                  //   every system is staged, else 0 (both
                                  //   products form the same bits)
@@ -311,6 +316,9 @@ struct fs_csr {
     uint8_t *d_lpat = nullptr;
     void *d_scols = nullptr;
     int32_t stage_max = 0;
+    // at least kTileRows rows per row pattern: multi-column products run on
+    // the matrix cores
+    bool row_tiles = false;
     bool stream_loc = false;       // positions too large for the caches
     int32_t *d_map = nullptr;
     int32_t *d_imap = nullptr;     // slot -> CSR position, -1 = padding
@@ -417,6 +425,10 @@ hipError_t launch_spmv_f64(const fs_csr *A, const double *x, double *y,
 hipError_t launch_spmm_f64(const fs_csr *A, int32_t k, const double *X,
                            int64_t ldx, double *Y, int64_t ldy,
                            const int32_t *yperm, hipStream_t s);
+// The same on the matrix cores (A->row_tiles, k >= 3).
+hipError_t launch_spmm_tiles(const fs_csr *A, int32_t k, const double *X,
+                             int64_t ldx, double *Y, int64_t ldy,
+                             const int32_t *yperm, hipStream_t s);
 // m products y_i = A_i x_i in caller numbering, descriptors passed as
 // kernel arguments (kBatchPerLaunch matrices per launch).
 constexpr int kBatchPerLaunch = 56;

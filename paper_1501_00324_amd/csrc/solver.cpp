@@ -195,7 +195,7 @@ fs_status batch_build(Batch &B, hipStream_t s, bool async_upload)
     std::vector<int32_t> smap, vmap;
     B.cols.clear();
     int32_t kmax = 1, sb = 0, vb = 0, stage = 0;
-    bool all_staged = true;
+    bool all_staged = true, all_tiles = true;
     for (int32_t i = 0; i < m; ++i) {
         CgSys &S = *B.members[size_t(i)];
         const fs_csr *A = S.A;
@@ -209,6 +209,9 @@ fs_status batch_build(Batch &B, hipStream_t s, bool async_upload)
         d.gbase = A->d_col16 ? A->d_gbase : nullptr;
         d.st = stage_of(A);
         all_staged &= A->stage_max > 0 || A->n_groups == 0;
+        // (31-bit offsets of the vectors' rows, tiles.h)
+        all_tiles &= A->n_groups == 0 ||
+                     (A->row_tiles && int64_t(S.n) * S.k < (int64_t(1) << 28) - 16);
         stage = std::max(stage, A->stage_max);
         d.n = S.n;
         d.ngroups = A->n_groups;
@@ -315,6 +318,7 @@ fs_status batch_build(Batch &B, hipStream_t s, bool async_upload)
     B.L.vblocks = vb;
     B.L.ncols = nc;
     B.L.stage = all_staged ? stage : 0;
+    B.L.tiles = all_tiles ? 1 : 0;
     if (B.graph) (void)hipGraphExecDestroy(B.graph);
     B.graph = nullptr;
     B.graph_iters = 0;

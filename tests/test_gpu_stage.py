@@ -97,3 +97,34 @@ def test_staged_low_precision(orc, name, dtype):
     xd = x.astype(np.float64)
     bound = (np.diff(A.rowptr).max() + 8) * 2.0 ** -24 * orc.spmv_abs(R, xd)
     assert np.all(np.abs(y - orc.spmv(R, xd)[perm]) <= bound[perm])
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("name", ["three", "six", "lanes", "empty", "wide", "far"])
+def test_tile_product(orc, name, k):
+    """Several columns, matrices whose rows share columns (matrix cores from
+    three columns on), row strides over k, both slot widths."""
+    note("tile product %s k=%d" % (name, k))
+    A = block_matrix(seed=13, **CASES[name])
+    for vec in (1, 2):
+        M = make(A, vec=vec)
+        X = np.random.default_rng(14).uniform(-1, 1, (A.n_cols, k))
+        Y = host(fs.spmm(M, dev(X)))
+        scale = np.stack([orc.spmv_abs(A, X[:, c]) for c in range(k)], 1)
+        assert_spmv_close(Y, orc.spmm(A, X), scale, "%s k=%d" % (name, k))
+
+
+@pytest.mark.parametrize("k", [4, 7, 16])
+def test_tile_padding_and_infinity(k):
+    """An infinity in one column of X stays in that column and in the rows
+    that reference it."""
+    note("tile infinity k=%d" % k)
+    A = block_matrix(seed=15, **CASES["three"])
+    M = make(A)
+    rows = np.repeat(np.arange(A.n_rows), np.diff(A.rowptr))
+    for j, c in ((0, 0), (A.n_cols // 2, k - 1), (A.n_cols - 1, 1)):
+        X = np.ones((A.n_cols, k))
+        X[j, c] = np.inf
+        hit = np.zeros((A.n_rows, k), bool)
+        hit[rows[A.col == j], c] = True
+        assert np.array_equal(~np.isfinite(host(fs.spmm(M, dev(X)))), hit)
