@@ -1249,7 +1249,10 @@ __global__ void k_gather_states(const SysDesc *__restrict__ sys,
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= ncols) return;
     const int2 sc = cmap[b];
-    staging[b] = sys[sc.x].cs[sc.y];
+    const SysDesc &S = sys[sc.x];
+    ColState c = S.cs[sc.y];
+    c.bad_diag = S.dinv ? *S.bad_diag : 0;
+    staging[b] = c;
 }
 
 // Row permutation of an n x k block: TO_LAYOUT dst[i, :] = src[perm[i], :],

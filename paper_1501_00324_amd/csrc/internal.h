@@ -126,7 +126,9 @@ struct ColState {                // one right-hand side, device resident
     double bnorm2, tol2;
     double rho_prev;             // rho of the previous iteration (fused path)
     int32_t iter, status, pending, maxit;
-    int32_t replacements, pad[3];
+    int32_t replacements;
+    int32_t bad_diag;            // host copies only: the system's bad rows
+    int32_t pad[2];
 };
 
 // One linear system of a batched launch, in layout numbering.  Vectors are
@@ -254,14 +256,17 @@ struct Batch {
     ColState *d_stage = nullptr, *h_stage = nullptr;
     int32_t cap_sys = 0, cap_s = 0, cap_v = 0, cap_c = 0;
     EngineLaunch L{};
-    hipGraphExec_t graph = nullptr;
-    int32_t graph_iters = 0;
+    // graphs of the two chunk lengths in use (iterations each); they hold
+    // device addresses and grid sizes only, so they last while L does
+    hipGraphExec_t graph[2] = {nullptr, nullptr};
+    int32_t graph_iters[2] = {0, 0};
     std::vector<int2> cols;           // (member, column) per finalize block
     // pinned staging of stream-ordered descriptor uploads, and the event
     // of the last upload
     void *h_up = nullptr;
     size_t up_cap = 0;
     hipEvent_t up_ev = nullptr;
+    std::vector<char> uploaded;       // what the device arrays hold
 };
 
 fs_status sys_alloc(CgSys &S, struct ::fs_csr *A, int32_t k, int32_t vt,
@@ -273,9 +278,9 @@ int64_t sys_block_bytes(const struct ::fs_csr *A, int32_t k, int32_t st,
 void sys_alloc_in(CgSys &S, struct ::fs_csr *A, int32_t k, int32_t vt,
                   int32_t st, int32_t precond, void *block);
 void sys_free(CgSys &S);
-fs_status batch_build(Batch &B, hipStream_t s);   // upload descs and maps
-// async_upload: stream-ordered upload from pinned staging, no host wait
-fs_status batch_build(Batch &B, hipStream_t s, bool async_upload);
+// descriptors and maps of the members, uploaded in stream order from pinned
+// staging where they differ from what the device holds
+fs_status batch_build(Batch &B, hipStream_t s);
 // gather the column states and copy them to h_stage, without waiting
 fs_status batch_stage_states(Batch &B, hipStream_t s);
 void batch_free(Batch &B);

@@ -288,7 +288,7 @@ fs_status step(fs_server *S)
         J.st = ST_F64;
         J.vec = 1 + cls / kKmClasses;
         const hipStream_t st = class_stream(S, cls);
-        FS_TRY(batch_build(J, st, true));
+        FS_TRY(batch_build(J, st));
         if (S->o.precond) FS_HIP_TRY(engine_diag_inv(J.L, st));
         FS_HIP_TRY(engine_residual(J.L, 0, true, st));
     }
@@ -314,7 +314,7 @@ fs_status step(fs_server *S)
             B.vt = VT_F64;
             B.st = ST_F64;
             B.vec = 1 + cls / kKmClasses;
-            FS_TRY(batch_build(B, st, true));
+            FS_TRY(batch_build(B, st));
             S->stable[cls] = 0;
         } else {
             S->stable[cls]++;

@@ -154,10 +154,21 @@ fs_status sys_alloc(CgSys &S, fs_csr *A, int32_t k, int32_t vt, int32_t st,
 }
 
 // --------------------------------------------------------------- batches
+namespace {
+void drop_graphs(Batch &B)
+{
+    for (int i = 0; i < 2; ++i) {
+        if (B.graph[i]) (void)hipGraphExecDestroy(B.graph[i]);
+        B.graph[i] = nullptr;
+        B.graph_iters[i] = 0;
+    }
+}
+}  // namespace
+
 void batch_free(Batch &B)
 {
-    if (B.graph) (void)hipGraphExecDestroy(B.graph);
-    B.graph = nullptr;
+    drop_graphs(B);
+    B.uploaded.clear();
     dfree(B.d_sys); dfree(B.d_smap); dfree(B.d_vmap); dfree(B.d_cmap);
     dfree(B.d_stage);
     if (B.h_stage) (void)hipHostFree(B.h_stage);
@@ -186,9 +197,7 @@ fs_status ensure_cap(T *&p, int32_t &cap, int32_t want)
 }
 }  // namespace
 
-fs_status batch_build(Batch &B, hipStream_t s) { return batch_build(B, s, false); }
-
-fs_status batch_build(Batch &B, hipStream_t s, bool async_upload)
+fs_status batch_build(Batch &B, hipStream_t s)
 {
     const int32_t m = int32_t(B.members.size());
     std::vector<SysDesc> descs(static_cast<size_t>(m));
@@ -258,70 +267,76 @@ fs_status batch_build(Batch &B, hipStream_t s, bool async_upload)
                                  hipHostMallocDefault));
         B.cap_c = cap;
     }
-    if (async_upload) {
+    // the device arrays of a repeated solve already hold these descriptors
+    std::vector<char> bytes(sizeof(SysDesc) * size_t(m) +
+                            sizeof(int32_t) * size_t(sb + vb) +
+                            sizeof(int2) * size_t(nc));
+    {
+        char *h = bytes.data();
+        auto put = [&](const void *src, size_t n) {
+            if (n) std::memcpy(h, src, n);
+            h += n;
+        };
+        put(descs.data(), sizeof(SysDesc) * size_t(m));
+        put(smap.data(), sizeof(int32_t) * size_t(sb));
+        put(vmap.data(), sizeof(int32_t) * size_t(vb));
+        put(B.cols.data(), sizeof(int2) * size_t(nc));
+    }
+    const bool same_arrays = B.L.sys == B.d_sys && B.L.smap == B.d_smap &&
+                             B.L.vmap == B.d_vmap && B.L.cmap == B.d_cmap;
+    if (!same_arrays || bytes != B.uploaded) {
         // stream-ordered copies from a pinned staging area of the batch:
         // the staging area is rewritten only once the previous upload has
         // completed (its event)
-        const size_t bytes = sizeof(SysDesc) * size_t(m) +
-                             sizeof(int32_t) * size_t(sb + vb) +
-                             sizeof(int2) * size_t(nc);
+        B.uploaded.clear();
         if (B.up_ev) FS_HIP_TRY(hipEventSynchronize(B.up_ev));
         else FS_HIP_TRY(hipEventCreateWithFlags(&B.up_ev,
                                                 hipEventDisableTiming));
-        if (bytes > B.up_cap) {
-            const size_t cap = std::max(bytes, 2 * B.up_cap);
+        if (bytes.size() > B.up_cap) {
+            const size_t cap = std::max(bytes.size(), 2 * B.up_cap);
             if (B.h_up) (void)hipHostFree(B.h_up);
             B.h_up = nullptr;
             B.up_cap = 0;
             FS_HIP_TRY(hipHostMalloc(&B.h_up, cap, hipHostMallocDefault));
             B.up_cap = cap;
         }
+        if (!bytes.empty()) std::memcpy(B.h_up, bytes.data(), bytes.size());
         char *h = static_cast<char *>(B.h_up);
-        auto put = [&](void *dst, const void *src, size_t n) -> hipError_t {
+        auto put = [&](void *dst, size_t n) -> hipError_t {
             if (!n) return hipSuccess;
-            std::memcpy(h, src, n);
             hipError_t e = hipMemcpyAsync(dst, h, n, hipMemcpyHostToDevice, s);
             h += n;
             return e;
         };
-        FS_HIP_TRY(put(B.d_sys, descs.data(), sizeof(SysDesc) * m));
-        FS_HIP_TRY(put(B.d_smap, smap.data(), sizeof(int32_t) * sb));
-        FS_HIP_TRY(put(B.d_vmap, vmap.data(), sizeof(int32_t) * vb));
-        FS_HIP_TRY(put(B.d_cmap, B.cols.data(), sizeof(int2) * nc));
+        FS_HIP_TRY(put(B.d_sys, sizeof(SysDesc) * m));
+        FS_HIP_TRY(put(B.d_smap, sizeof(int32_t) * sb));
+        FS_HIP_TRY(put(B.d_vmap, sizeof(int32_t) * vb));
+        FS_HIP_TRY(put(B.d_cmap, sizeof(int2) * nc));
         FS_HIP_TRY(hipEventRecord(B.up_ev, s));
-    } else {
-        // blocking copies: the host vectors are temporaries
-        FS_HIP_TRY(hipStreamSynchronize(s));
-        if (m) FS_HIP_TRY(hipMemcpy(B.d_sys, descs.data(),
-                                    sizeof(SysDesc) * m,
-                                    hipMemcpyHostToDevice));
-        if (sb) FS_HIP_TRY(hipMemcpy(B.d_smap, smap.data(),
-                                     sizeof(int32_t) * sb,
-                                     hipMemcpyHostToDevice));
-        if (vb) FS_HIP_TRY(hipMemcpy(B.d_vmap, vmap.data(),
-                                     sizeof(int32_t) * vb,
-                                     hipMemcpyHostToDevice));
-        if (nc) FS_HIP_TRY(hipMemcpy(B.d_cmap, B.cols.data(),
-                                     sizeof(int2) * nc,
-                                     hipMemcpyHostToDevice));
+        B.uploaded = std::move(bytes);
     }
+    EngineLaunch L{};
     B.km = km_for(kmax);
-    B.L.vt = B.vt;
-    B.L.st = B.st;
-    B.L.vec = B.vec;
-    B.L.km = B.km;
-    B.L.sys = B.d_sys;
-    B.L.smap = B.d_smap;
-    B.L.vmap = B.d_vmap;
-    B.L.cmap = B.d_cmap;
-    B.L.sblocks = sb;
-    B.L.vblocks = vb;
-    B.L.ncols = nc;
-    B.L.stage = all_staged ? stage : 0;
-    B.L.tiles = all_tiles ? 1 : 0;
-    if (B.graph) (void)hipGraphExecDestroy(B.graph);
-    B.graph = nullptr;
-    B.graph_iters = 0;
+    L.vt = B.vt;
+    L.st = B.st;
+    L.vec = B.vec;
+    L.km = B.km;
+    L.sys = B.d_sys;
+    L.smap = B.d_smap;
+    L.vmap = B.d_vmap;
+    L.cmap = B.d_cmap;
+    L.sblocks = sb;
+    L.vblocks = vb;
+    L.ncols = nc;
+    L.stage = all_staged ? stage : 0;
+    L.tiles = all_tiles ? 1 : 0;
+    auto key = [](const EngineLaunch &l) {
+        return std::make_tuple(l.vt, l.st, l.vec, l.km, l.sys, l.smap, l.vmap,
+                               l.cmap, l.sblocks, l.vblocks, l.ncols, l.tiles,
+                               l.stage);
+    };
+    if (key(L) != key(B.L)) drop_graphs(B);
+    B.L = L;
     return FS_OK;
 }
 
@@ -334,9 +349,12 @@ fs_status batch_iterations(Batch &B, int32_t iters, bool use_graph,
             FS_HIP_TRY(engine_iteration(B.L, s));
         return FS_OK;
     }
-    if (!B.graph || B.graph_iters != iters) {
-        if (B.graph) (void)hipGraphExecDestroy(B.graph);
-        B.graph = nullptr;
+    int slot = B.graph_iters[0] == iters ? 0 : B.graph_iters[1] == iters ? 1 : -1;
+    if (slot < 0) {
+        slot = B.graph[0] && !B.graph[1] ? 1 : 0;
+        if (B.graph[slot]) (void)hipGraphExecDestroy(B.graph[slot]);
+        B.graph[slot] = nullptr;
+        B.graph_iters[slot] = 0;
         hipGraph_t g = nullptr;
         FS_HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
         hipError_t e = hipSuccess;
@@ -348,16 +366,16 @@ fs_status batch_iterations(Batch &B, int32_t iters, bool use_graph,
             return set_error(FS_E_HIP, "graph capture: %s",
                              hipGetErrorString(e != hipSuccess ? e : e2));
         }
-        e = hipGraphInstantiate(&B.graph, g, nullptr, nullptr, 0);
+        e = hipGraphInstantiate(&B.graph[slot], g, nullptr, nullptr, 0);
         (void)hipGraphDestroy(g);
         if (e != hipSuccess) {
-            B.graph = nullptr;
+            B.graph[slot] = nullptr;
             return set_error(FS_E_HIP, "graph instantiate: %s",
                              hipGetErrorString(e));
         }
-        B.graph_iters = iters;
+        B.graph_iters[slot] = iters;
     }
-    FS_HIP_TRY(hipGraphLaunch(B.graph, s));
+    FS_HIP_TRY(hipGraphLaunch(B.graph[slot], s));
     return FS_OK;
 }
 
@@ -388,34 +406,96 @@ bool any_status(const Batch &B, int32_t st)
     return false;
 }
 
+// The chunks between two looks at the column states.  A solve used to launch
+// check_every iterations at a time, whatever was left to do: a solve of 35
+// iterations launched 64, refinement steps of 9 launched 32 each (an idle
+// iteration of three empty launches takes 5-7 us).  Now the columns' rate
+// of convergence says how many are left; a look never comes later than
+// every check_every iterations, and at each multiple of it, as before.
+// Chunks are multiples of kChunk iterations, replayed as graphs of kChunk
+// and kLongChunk, which the batch keeps.
+constexpr int32_t kChunk = 4, kLongChunk = 16;
+struct Pace {
+    int32_t every = 32;
+    int32_t since = 0;                    // iterations since the start
+    std::vector<double> rr, rate;         // per column: |r|^2 at the last
+    std::vector<int32_t> iter;            //   look, its fall per iteration
+    // iterations of the next chunk, from the states of the last look
+    int32_t next(const Batch &B)
+    {
+        const size_t nc = size_t(B.L.ncols);
+        if (rr.size() != nc) {
+            rr.assign(nc, 0.0);
+            rate.assign(nc, 0.0);
+            iter.assign(nc, 0);
+        }
+        double want = kChunk;
+        for (size_t c = 0; c < nc; ++c) {
+            const ColState &s = B.h_stage[c];
+            if (s.status == CG_RUNNING && s.rr > 0.0 && s.tol2 > 0.0) {
+                const double left = std::log(s.rr / s.tol2);
+                if (s.iter > iter[c] && rr[c] > s.rr && since > 0)
+                    rate[c] = std::log(rr[c] / s.rr) / (s.iter - iter[c]);
+                // unknown rate: two iterations per digit of |r|
+                const double it = rate[c] > 0.0 ? left / rate[c]
+                                                : 0.434 * left;
+                if (it > want) want = it;
+            }
+            rr[c] = s.rr;
+            iter[c] = s.iter;
+        }
+        const int32_t room = every - since % every;
+        int32_t n = room;
+        if (every % kChunk == 0 && want < room)
+            n = std::min(room, (int32_t(std::ceil(want)) + kChunk - 1) /
+                                   kChunk * kChunk);
+        since += n;
+        return n;
+    }
+};
+
+// n iterations for every running column of B, in kept graphs.
+fs_status batch_chunk(Batch &B, int32_t n, bool use_graph, hipStream_t s)
+{
+    if (!use_graph || n % kChunk != 0) return batch_iterations(B, n, use_graph, s);
+    for (; n >= kLongChunk; n -= kLongChunk)
+        FS_TRY(batch_iterations(B, kLongChunk, true, s));
+    for (; n > 0; n -= kChunk) FS_TRY(batch_iterations(B, kChunk, true, s));
+    return FS_OK;
+}
+
+// Jacobi scaling and the start residual (mode 0) of every member, with the
+// states read; zero or non-finite diagonals are an error.
+fs_status start_batch(Batch &B, bool x_zero, hipStream_t s)
+{
+    FS_TRY(batch_build(B, s));
+    bool pc = false;
+    for (CgSys *S : B.members) {
+        if (!S->precond) continue;
+        pc = true;
+        FS_HIP_TRY(hipMemsetAsync(S->bad, 0, sizeof(int32_t), s));
+    }
+    if (pc) FS_HIP_TRY(engine_diag_inv(B.L, s));
+    FS_HIP_TRY(engine_residual(B.L, 0, x_zero, s));
+    FS_TRY(batch_read_states(B, s));
+    for (int32_t i = 0; i < B.L.ncols; ++i)
+        if (B.h_stage[i].bad_diag)
+            return set_error(FS_E_ARG,
+                             "Jacobi preconditioner: %d rows with a zero "
+                             "or non-finite diagonal", B.h_stage[i].bad_diag);
+    return FS_OK;
+}
+
 // Run every member of B from its current x to convergence (or failure).
 // Members' b and x are set, rtol / maxit / precond are in the members.
 fs_status run_batch(Batch &B, int32_t check_every, bool use_graph,
                     bool x_zero, hipStream_t s)
 {
-    FS_TRY(batch_build(B, s));
-    bool pc = false;
-    for (CgSys *S : B.members) pc |= S->precond != 0;
-    if (pc) {
-        for (CgSys *S : B.members)
-            FS_HIP_TRY(hipMemsetAsync(S->bad, 0, sizeof(int32_t), s));
-        FS_HIP_TRY(engine_diag_inv(B.L, s));
-        for (CgSys *S : B.members) {
-            if (!S->precond) continue;
-            int32_t bad = 0;
-            FS_HIP_TRY(hipMemcpyAsync(&bad, S->bad, sizeof bad,
-                                      hipMemcpyDeviceToHost, s));
-            FS_HIP_TRY(hipStreamSynchronize(s));
-            if (bad)
-                return set_error(FS_E_ARG,
-                                 "Jacobi preconditioner: %d rows with a zero "
-                                 "or non-finite diagonal", bad);
-        }
-    }
-    FS_HIP_TRY(engine_residual(B.L, 0, x_zero, s));
-    FS_TRY(batch_read_states(B, s));
+    FS_TRY(start_batch(B, x_zero, s));
+    Pace pace;
+    pace.every = check_every;
     while (any_status(B, CG_RUNNING)) {
-        FS_TRY(batch_iterations(B, check_every, use_graph, s));
+        FS_TRY(batch_chunk(B, pace.next(B), use_graph, s));
         FS_TRY(batch_read_states(B, s));
         if (any_status(B, CG_RECURRENCE_MET)) {
             FS_HIP_TRY(engine_residual(B.L, 1, false, s));
@@ -648,30 +728,6 @@ fs_status solve_f64(fs_csr *A, int32_t k, const double *Bc, int64_t ldb,
     return ret;
 }
 
-// Start a batch's CG from x = 0 without iterating: Jacobi scaling (checked)
-// and the start residual r = b, p = z.
-fs_status start_inner(Batch &B, bool precond, hipStream_t s)
-{
-    FS_TRY(batch_build(B, s));
-    if (precond) {
-        for (CgSys *S : B.members)
-            FS_HIP_TRY(hipMemsetAsync(S->bad, 0, sizeof(int32_t), s));
-        FS_HIP_TRY(engine_diag_inv(B.L, s));
-        for (CgSys *S : B.members) {
-            int32_t bad = 0;
-            FS_HIP_TRY(hipMemcpyAsync(&bad, S->bad, sizeof bad,
-                                      hipMemcpyDeviceToHost, s));
-            FS_HIP_TRY(hipStreamSynchronize(s));
-            if (bad)
-                return set_error(FS_E_ARG,
-                                 "Jacobi preconditioner: %d rows with a zero "
-                                 "or non-finite diagonal", bad);
-        }
-    }
-    FS_HIP_TRY(engine_residual(B.L, 0, true, s));
-    return batch_read_states(B, s);
-}
-
 // Mixed-precision iterative refinement: FP64 residual and update, inner CG
 // on the FP32 / BF16 copy of A with float vectors.
 fs_status solve_ir(fs_csr *A, int32_t k, const double *Bc, int64_t ldb,
@@ -765,6 +821,7 @@ fs_status solve_ir(fs_csr *A, int32_t k, const double *Bc, int64_t ldb,
     int32_t fresh_iters = 0;
     std::vector<ColState> last(static_cast<size_t>(k));
     double prev_rr = 0.0;
+    Pace pace;                 // of the inner iterations, over all steps
     for (;;) {
         // FP64 residual r = b - A x and its norm against rtol |b|
         FS_HIP_TRY(engine_residual(BO.L, 0, x_zero, s));
@@ -814,7 +871,7 @@ fs_status solve_ir(fs_csr *A, int32_t k, const double *Bc, int64_t ldb,
         if (fresh || o.ir_restart) {
             inner_base = inner_total;
             In.maxit = std::max(1, o.maxit - inner_base);
-            FS_TRY(start_inner(BI, in_pc, s));
+            FS_TRY(start_batch(BI, true, s));
             fresh = false;
             last_fresh = true;
         } else {
@@ -830,8 +887,10 @@ fs_status solve_ir(fs_csr *A, int32_t k, const double *Bc, int64_t ldb,
         int32_t seg0 = 0;
         for (int32_t c = 0; c < k; ++c)
             seg0 = std::max(seg0, BI.h_stage[c].iter);
+        pace.every = o.check_every;
+        pace.since = 0;
         while (any_status(BI, CG_RUNNING)) {
-            if (!last_fresh) {
+            if (!last_fresh && pace.since % pace.every == 0) {
                 int32_t itn = 0;
                 for (int32_t c = 0; c < k; ++c)
                     itn = std::max(itn, BI.h_stage[c].iter);
@@ -840,7 +899,7 @@ fs_status solve_ir(fs_csr *A, int32_t k, const double *Bc, int64_t ldb,
                     break;
                 }
             }
-            FS_TRY(batch_iterations(BI, o.check_every, o.use_graph != 0, s));
+            FS_TRY(batch_chunk(BI, pace.next(BI), o.use_graph != 0, s));
             FS_TRY(batch_read_states(BI, s));
             if (o.ir_restart && any_status(BI, CG_RECURRENCE_MET)) {
                 // classic refinement confirms the inner solve against its own
