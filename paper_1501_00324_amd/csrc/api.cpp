@@ -24,7 +24,7 @@ void free_handle(fs_csr *A)
     dfree(A->d_val_bf16); dfree(A->d_col); dfree(A->d_map); dfree(A->d_imap);
     dfree(A->d_jpos); dfree(A->d_rstart);
     dfree(A->d_col16); dfree(A->d_gbase);
-    dfree(A->d_sgrp); dfree(A->d_loc); dfree(A->d_lpat); dfree(A->d_scols);
+    dfree(A->d_diag); dfree(A->d_sgrp); dfree(A->d_loc); dfree(A->d_lpat); dfree(A->d_scols);
     dfree(A->d_perm); dfree(A->d_iperm); dfree(A->d_xtmp); dfree(A->d_Xtmp);
 }
 
@@ -109,7 +109,8 @@ fs_status build_refresh_rows(fs_csr *A, const int32_t *h_rp, int64_t &acct,
     return FS_OK;
 }
 
-// Arrays of the staged products (internal.h: StageGroup), kept when every
+// The diagonal's slots (square matrices), and the arrays of the staged
+// products (internal.h: StageGroup), kept when every
 // group has at most kStageMax distinct columns and the matrix at most
 // kStageMost of them per slot: a staged group gathers each column once
 // instead of once per slot, and reads its list on top.  After the slot
@@ -118,6 +119,11 @@ fs_status build_refresh_rows(fs_csr *A, const int32_t *h_rp, int64_t &acct,
 fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
 {
     const size_t ng = size_t(A->n_groups);
+    if (A->n_rows == A->n_cols && ng > 0) {
+        FS_TRY(dalloc(&A->d_diag, A->n_rows, acct));
+        FS_HIP_TRY(launch_diag_slots(A->d_groups, A->n_groups, A->host.vec,
+                                     A->d_col, A->d_diag, s));
+    }
     if (ng == 0 || A->slots == 0) return FS_OK;
     const bool narrow = A->d_gbase != nullptr;
     int64_t bytes = 0;

@@ -182,6 +182,30 @@ __global__ __launch_bounds__(kBlock) void k_offsets16(
     }
 }
 
+// Slot of every row's diagonal entry, -1 where it has none (one wavefront
+// per row group): the Jacobi scaling of a solve then reads one value per row
+// instead of searching the columns.
+__global__ __launch_bounds__(kBlock) void k_diag_slots(
+    const Group *__restrict__ groups, int ngroups, int V,
+    const int *__restrict__ slot_col, int *__restrict__ diag)
+{
+    const int g = int(blockIdx.x) * kWavesPerBlock + int(threadIdx.x >> 6);
+    if (g >= ngroups) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const Group G = load_group(gbl(groups), g);
+    const long base = long(G.base64) * kWave;
+    const int width = G.width_lt & 0xffffff, lt = G.width_lt >> 24;
+    const int r = lane >> lt;
+    int at = -1;
+    for (int s = 0; s < width; ++s) {
+        const long i = base + long(s / V) * kWave * V + lane * V + s % V;
+        if (slot_col[i] == G.row0 + r) at = int(i);
+    }
+    for (int o = 1; o < (1 << lt); o <<= 1)
+        at = max(at, __shfl_xor(at, o, kWave));
+    if ((lane & ((1 << lt) - 1)) == 0 && r < G.nrows) diag[G.row0 + r] = at;
+}
+
 // ------------------------------------------------------ staged products
 // Both kernels run one wavefront per workgroup and row group and find the
 // group's distinct columns with a bitmap over its column span in LDS.
@@ -554,6 +578,16 @@ hipError_t launch_assign_slots(const Group *groups, int32_t ngroups,
     hipLaunchKernelGGL(k_assign_slots, dim3(wave_grid(ngroups)), dim3(kBlock),
                        0, s, groups, ngroups, vec, perm, iperm, rowptr, col,
                        slot_col, map, lohi, dup);
+    return hipGetLastError();
+}
+
+hipError_t launch_diag_slots(const Group *groups, int32_t ngroups, int32_t vec,
+                             const int32_t *slot_col, int32_t *diag,
+                             hipStream_t s)
+{
+    if (ngroups == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_diag_slots, dim3(spmv_blocks(ngroups)), dim3(kBlock),
+                       0, s, groups, ngroups, vec, slot_col, diag);
     return hipGetLastError();
 }
 

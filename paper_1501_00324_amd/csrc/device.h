@@ -50,10 +50,66 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblk)
     return xcd * base + (xcd < rem ? xcd : rem) + idx;
 }
 
+// v of another lane, by a data-parallel-primitive control (a VALU move, where
+// a cross-lane shuffle is an LDS access of some 60 cycles).
+template <int CTRL> __device__ __forceinline__ double dpp(double v)
+{
+    const int2 w = __builtin_bit_cast(int2, v);
+    return __builtin_bit_cast(
+        double, make_int2(__builtin_amdgcn_update_dpp(0, w.x, CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, w.y, CTRL, 0xf, 0xf, true)));
+}
+template <int CTRL> __device__ __forceinline__ float dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(
+        0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e;   // quad_perm 1,0,3,2 / 2,3,0,1
+constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;
+
+// v plus v of lane ^ 16 or lane ^ 32 (the swaps exchange 16- or 32-lane rows
+// between their two results).
+template <int O> __device__ __forceinline__ unsigned swap_rows(unsigned v, unsigned &w)
+{
+    if constexpr (O == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        w = r[1];
+        return r[0];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        w = r[1];
+        return r[0];
+    }
+}
+template <int O> __device__ __forceinline__ double add_rows(double v)
+{
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    uint2 a, b;
+    a.x = swap_rows<O>(u.x, b.x);
+    a.y = swap_rows<O>(u.y, b.y);
+    return __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
+}
+template <int O> __device__ __forceinline__ float add_rows(float v)
+{
+    unsigned b;
+    const unsigned a = swap_rows<O>(__float_as_uint(v), b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+
+// Butterfly over the lane distances 32, 16, ..., 1 (all lanes active): the
+// sums of the shuffle form, bit for bit -- once the distance-8 sums are
+// equal, a rotation by 4 in a row of 16 is the distance-4 partner.  A
+// six-step shuffle butterfly of a double takes about 0.35 us in a kernel
+// that waits for it, this one about 0.06.
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    v = add_rows<32>(v);
+    v = add_rows<16>(v);
+    v += dpp<kDppRor8>(v);
+    v += dpp<kDppRor4>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppXor1>(v);
     return v;
 }
 
@@ -261,11 +317,18 @@ __device__ __forceinline__ double group_lane_sum_plain(const Group &g,
     return acc0 + acc1;
 }
 
-// Sum over the T = 2^lt lanes of each row (lanes of a row are adjacent).
+// Sum over the T = 2^lt lanes of each row (lanes of a row are adjacent), lane
+// distances 1, 2, ..., T / 2; mirrors stand for the distances 4 and 8, whose
+// partners hold equal sums by then.
 template <typename T>
 __device__ __forceinline__ T row_reduce(T acc, int lt)
 {
-    for (int o = 1; o < (1 << lt); o <<= 1) acc += __shfl_xor(acc, o, kWave);
+    if (lt > 0) acc += dpp<kDppXor1>(acc);
+    if (lt > 1) acc += dpp<kDppXor2>(acc);
+    if (lt > 2) acc += dpp<kDppHalfMirror>(acc);
+    if (lt > 3) acc += dpp<kDppMirror>(acc);
+    if (lt > 4) acc = add_rows<16>(acc);
+    if (lt > 5) acc = add_rows<32>(acc);
     return acc;
 }
 

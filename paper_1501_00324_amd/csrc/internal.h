@@ -146,6 +146,7 @@ struct SysDesc {
     void *x, *r, *p, *q;
     const void *b, *dinv;        // dinv NULL: no preconditioner
     ColState *cs;                // k entries
+    const int32_t *diag;         // slot of each row's diagonal, -1: none
     int32_t *bad_diag;           // rows with a zero / non-finite diagonal
     double *partials;            // 3 * k * max(snb, vnb) entries
     double rtol;
@@ -324,6 +325,8 @@ struct fs_csr {
     // at least kTileRows rows per row pattern: multi-column products run on
     // the matrix cores
     bool row_tiles = false;
+    int32_t *d_diag = nullptr;     // slot of each layout row's diagonal, -1:
+                                   //   none (square matrices)
     bool stream_loc = false;       // positions too large for the caches
     int32_t *d_map = nullptr;
     int32_t *d_imap = nullptr;     // slot -> CSR position, -1 = padding
@@ -414,6 +417,10 @@ hipError_t launch_stage_count(const Group *groups, int32_t ngroups,
                               int32_t vec, const int32_t *slot_col,
                               bool narrow, uint8_t *lpat, int2 *counts,
                               hipStream_t s);
+// Slot of every layout row's diagonal entry (-1: none).
+hipError_t launch_diag_slots(const Group *groups, int32_t ngroups, int32_t vec,
+                             const int32_t *slot_col, int32_t *diag,
+                             hipStream_t s);
 hipError_t launch_stage_lists(const Group *groups, int32_t ngroups,
                               int32_t vec, const int32_t *slot_col,
                               const int32_t *gbase, const StageGroup *grp,

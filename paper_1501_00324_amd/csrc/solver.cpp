@@ -234,6 +234,7 @@ fs_status batch_build(Batch &B, hipStream_t s)
         d.b = S.b;
         d.dinv = S.precond ? S.dinv : nullptr;
         d.cs = S.cs;
+        d.diag = A->d_diag;
         d.bad_diag = S.bad;
         d.partials = S.partials;
         d.rtol = S.rtol;
