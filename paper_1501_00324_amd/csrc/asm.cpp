@@ -196,11 +196,38 @@ fs_status upload_lds(const HostLds &H, AsmLdsPlan &D, int64_t &acct,
     D.nbatch = int64_t(H.bdesc.size() / 2);
     D.nrec = int64_t(H.off.size() / kWave);
     D.contrib = H.contrib;
+    D.big = 8 * H.contrib > kAsmBig;
     FS_TRY(upload(&D.d_gdesc, H.gdesc, acct, s));
-    FS_TRY(upload(&D.d_bdesc, H.bdesc, acct, s));
     FS_TRY(upload(&D.d_ea, H.ea, acct, s));
-    FS_TRY(upload(&D.d_off, H.off, acct, s));
-    return FS_OK;
+    // batch descriptors with the offsets' new places, then the offsets four
+    // steps to an entry
+    Buf bd;
+    bd.alloc(size_t(4 * D.nbatch));
+    int64_t at = 0;
+    for (int64_t b = 0; b < D.nbatch; ++b) {
+        const int32_t *h = H.bdesc.data() + 2 * b;
+        int32_t *o = bd.data() + 4 * b;
+        o[0] = h[0];
+        o[1] = h[1];
+        o[2] = int32_t(at);
+        o[3] = 0;
+        at += (h[1] + 3) / 4;
+    }
+    FS_TRY(upload(&D.d_bdesc, bd, acct, s));
+    FS_TRY(dalloc(&D.d_off, at * 4 * kWave, acct));
+    uint16_t *raw = nullptr;
+    int64_t scratch = 0;
+    fs_status st = upload(&raw, H.off, scratch, s);
+    if (st == FS_OK) {
+        const hipError_t e =
+            launch_interleave_offsets(D.d_bdesc, D.nbatch, raw, D.d_off, s);
+        const hipError_t e2 = hipStreamSynchronize(s);
+        if (e != hipSuccess || e2 != hipSuccess)
+            st = set_error(FS_E_HIP, "interleave offsets: %s",
+                           hipGetErrorString(e != hipSuccess ? e : e2));
+    }
+    dfree(raw);
+    return st;
 }
 
 fs_status upload_plan(const HostPlan &H, AsmPlan &D, int64_t &acct,

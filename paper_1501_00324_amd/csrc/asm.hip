@@ -9,6 +9,8 @@
 // contribution count so the lists of one wavefront have nearly equal length,
 // and the element values are gathered through the cache hierarchy (a line
 // of an element matrix serves neighbouring rows of the same node).
+#include <type_traits>
+
 #include "device.h"
 
 namespace fs {
@@ -65,60 +67,34 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
     }
 }
 
-// U consecutive steps of one batch: lane q*nde + b adds element value
-// (ea_q * nde + b) into LDS slot off.  Every load is unconditional (indices
-// clamped) and lanes without work add 0.0 into a private dummy slot past
-// the group region, so the loop has no divergent branches.  With WR the
-// first lane of row q also adds element vector entry ea_q into racc.  With
-// ORD the element rows come from a buffer stored in the plan's own order
-// (row rec * rows + q), so they are read contiguously and ea is not needed.
-template <int U, bool WR, bool ORD>
-__device__ __forceinline__ void lds_steps(long rec, int lane, int qc,
-                                          bool act, int b, int nde, int rows,
-                                          int dummy,
-                                          const int *__restrict__ ea,
-                                          const uint16_t *__restrict__ off,
-                                          const double *__restrict__ ke,
-                                          const double *__restrict__ re,
-                                          double *acc, double &racc)
+// Place in LDS of a group's slot: one double of padding per 64, so that the
+// entries of a row, which lie 64 or 128 doubles apart, fall into different
+// banks (unpadded, conflicts took 62% of the LDS cycles).
+__device__ __forceinline__ int lds_place(int slot) { return slot + (slot >> 6); }
+__device__ __forceinline__ uint16_t lds_place(uint16_t off)
 {
-    int o[U], e[U];
-    double v[U];
+    return off == 0xffff ? off : uint16_t(lds_place(int(off)));
+}
+
+// LDS offsets of four steps of a lane side by side: out[(ob + c) * 64 + lane]
+// holds steps 4c .. 4c + 3 of the batch (0xffff past its last step), one
+// wavefront per batch.
+__global__ __launch_bounds__(kBlock) void k_interleave_offsets(
+    const int4 *__restrict__ bdesc, long nbatch,
+    const uint16_t *__restrict__ off, us4 *__restrict__ out)
+{
+    const long b = long(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
+    if (b >= nbatch) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int4 d = bdesc[b];
+    for (int c = 0; 4 * c < d.y; ++c) {
+        us4 o;
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-        o[u] = int(__builtin_nontemporal_load(off + (rec + u) * kWave + lane));
-    if constexpr (!ORD) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            e[u] = __builtin_nontemporal_load(ea + (rec + u) * rows + qc);
-    }
-    double w[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if constexpr (ORD) {
-            // rows of dropped element rows carry offsets 0xffff only
-            const bool use = act && o[u] != 0xffff;
-            v[u] = __builtin_nontemporal_load(
-                ke + ((rec + u) * rows + qc) * nde + b);
-            v[u] = use ? v[u] : 0.0;
-            o[u] = use ? o[u] : dummy;
-            continue;
-        }
-        const bool use = act && e[u] >= 0 && o[u] != 0xffff;
-        v[u] = ke[long(use ? e[u] : 0) * nde + b];
-        v[u] = use ? v[u] : 0.0;
-        o[u] = use ? o[u] : dummy;
-        if constexpr (WR) {
-            const bool ur = act && b == 0 && e[u] >= 0;
-            w[u] = re[ur ? e[u] : 0];
-            w[u] = ur ? w[u] : 0.0;
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) acc[o[u]] += v[u];
-    if constexpr (WR) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) racc += w[u];
+        for (int t = 0; t < 4; ++t)
+            o[t] = 4 * c + t < d.y
+                       ? lds_place(off[(long(d.x) + 4 * c + t) * kWave + lane])
+                       : uint16_t(0xffff);
+        out[(long(d.z) + c) * kWave + lane] = o;
     }
 }
 
@@ -132,50 +108,157 @@ __device__ __forceinline__ void lds_steps(long rec, int lane, int qc,
 // contributions in ascending element order.  With WR the element vectors
 // are assembled in the same pass: row q of a batch adds re[ea_q] at every
 // step (again element order) and writes r at its caller row perm[row].
-template <int U, bool WR, bool ORD>
+//
+// What bounds it is the address unit (four lanes a cycle, whatever they
+// load) and one chain of loads -- index, then value -- per eight steps.  So
+// a lane's LDS offsets come four steps to a load, the element rows of eight
+// steps (8 rows <= 64 of them, EA1) as one load of which every lane takes
+// its steps by shuffles, their vector entries likewise; and the indices of
+// the next eight steps are in flight while the values of these are waited
+// for.  12 (11 without the vector) load instructions per eight steps instead
+// of 32 (24).  Steps past a batch's last one are skipped, lanes without work
+// add 0.0 into a private dummy slot past the group region.  With ORD the
+// element rows come from a buffer stored in the plan's own order (row
+// rec * rows + q), so they are read contiguously and ea is not needed.
+//
+// BIG: element matrices larger together than the last-level cache.  An
+// element is read by the groups of all its nodes, about a level of the
+// locality order apart; with one contiguous range per XCD the eight windows
+// do not fit that cache and elements are fetched again (3.53 GB fetched for
+// 2.3 GB on the P1 elasticity 64^3 mesh), so the XCDs take chunks of 32
+// groups side by side, and the values stream out past the caches.  Smaller
+// data keeps the contiguous ranges (P1 Laplacian 70^3, 252 MB: 203 us, 218
+// in chunks).
+template <bool WR, bool ORD, bool EA1, bool BIG>
 __global__ __launch_bounds__(kBlock) void k_assemble_lds(
-    const int4 *__restrict__ gdesc, const int2 *__restrict__ bdesc,
-    const int *__restrict__ ea, const uint16_t *__restrict__ off, int nde,
+    const int4 *__restrict__ gdesc, const int4 *__restrict__ bdesc,
+    const int *__restrict__ ea, const us4 *__restrict__ off, int nde,
     int rows, const double *__restrict__ ke, double *__restrict__ val,
     float *__restrict__ f32, uint16_t *__restrict__ bf16,
     const Group *__restrict__ groups, const int *__restrict__ perm,
     const double *__restrict__ re, double *__restrict__ r)
 {
+    constexpr int U = 8;
     extern __shared__ double acc[];   // group region + 64 dummy slots
-    const int g = xcd_remap(blockIdx.x, gridDim.x);
+    int g;
+    if constexpr (BIG) {
+        constexpr int C = 32, R = 8 * C;   // chunk, groups per round of XCDs
+        const int i = int(blockIdx.x), whole = int(gridDim.x) / R * R;
+        g = i < whole ? i / R * R + i % 8 * C + i % R / 8 : i;
+    } else {
+        g = xcd_remap(blockIdx.x, gridDim.x);
+    }
     const int4 gd = gdesc[g];
-    const int region = gd.y * kWave;
-    for (int t = threadIdx.x; t < region; t += kBlock) acc[t] = 0.0;
+    const int region = gd.y * kWave, held = lds_place(region);
+    for (int t = threadIdx.x; t < held; t += kBlock) acc[t] = 0.0;
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int lane = threadIdx.x & (kWave - 1);
     const int q = lane / nde, b = lane - q * nde;
     const bool act = q < rows;
     const int qc = act ? q : rows - 1;
-    const int dummy = region + lane;
-    for (int j = wave; j < gd.w; j += kWavesPerBlock) {
-        const int2 bd = bdesc[gd.z + j];
-        const long r0 = __builtin_amdgcn_readfirstlane(bd.x);
-        const int K = __builtin_amdgcn_readfirstlane(bd.y);
+    const int dummy = held + lane;
+    const auto pe = gbl(ea);
+    const auto po = gbl(off);
+    const auto pk = gbl(ke);
+    // indices of the eight steps from k of batch d
+    struct Index {
+        us4 o[2];
+        int e[EA1 ? 1 : U];
+    };
+    auto batch = [&](int j) {
+        const int4 d = bdesc[gd.z + min(j, gd.w - 1)];
+        return make_int4(__builtin_amdgcn_readfirstlane(d.x),
+                         __builtin_amdgcn_readfirstlane(d.y),
+                         __builtin_amdgcn_readfirstlane(d.z), 0);
+    };
+    auto load = [&](Index &x, const int4 &d, int k) {
+        const auto p = po + (long(d.z) + (k >> 2)) * kWave + lane;
+        x.o[0] = __builtin_nontemporal_load(p);
+        if (k + 4 < d.y) x.o[1] = __builtin_nontemporal_load(p + kWave);
+        if constexpr (!ORD && EA1) {
+            // lane u * rows + q: step u of row q (past the batch: its last)
+            const int i = min(k * rows + lane, d.y * rows - 1);
+            x.e[0] = __builtin_nontemporal_load(pe + long(d.x) * rows + i);
+        } else if constexpr (!ORD) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k + u < d.y)
+                    x.e[u] = __builtin_nontemporal_load(
+                        pe + (long(d.x) + k + u) * rows + qc);
+        }
+    };
+    int j = wave;
+    int4 d = batch(j), dn = batch(j + kWavesPerBlock);
+    Index nx;
+    if (j < gd.w && d.y > 0) load(nx, d, 0);
+    for (; j < gd.w; j += kWavesPerBlock) {
         double racc = 0.0;
-        int k = 0;
-        for (; k + U <= K; k += U)
-            lds_steps<U, WR, ORD>(r0 + k, lane, qc, act, b, nde, rows, dummy,
-                                  ea, off, ke, re, acc, racc);
-        for (; k < K; ++k)
-            lds_steps<1, WR, ORD>(r0 + k, lane, qc, act, b, nde, rows, dummy,
-                                  ea, off, ke, re, acc, racc);
+        for (int k = 0; k < d.y; k += U) {
+            const Index x = nx;
+            int o[U], e[U];
+            double v[U], w = 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                o[u] = x.o[u >> 2][u & 3];
+                if (u >= 4 && k + 4 >= d.y) o[u] = 0xffff;
+                if constexpr (ORD) e[u] = 0;
+                else if constexpr (EA1) e[u] = __shfl(x.e[0], u * rows + qc, kWave);
+                else e[u] = k + u < d.y ? x.e[u] : -1;
+            }
+            if constexpr (WR && EA1) {
+                const bool ok = lane < U * rows && x.e[0] >= 0;
+                w = ok ? gbl(re)[x.e[0]] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                v[u] = 0.0;
+                if (k + u >= d.y) continue;
+                const bool use = act && o[u] != 0xffff && (ORD || e[u] >= 0);
+                if constexpr (ORD) {
+                    // rows of dropped element rows carry offsets 0xffff only
+                    v[u] = __builtin_nontemporal_load(
+                        pk + ((long(d.x) + k + u) * rows + qc) * nde + b);
+                } else {
+                    v[u] = pk[long(use ? e[u] : 0) * nde + b];
+                }
+                v[u] = use ? v[u] : 0.0;
+                o[u] = use ? o[u] : dummy;
+            }
+            double wu[U];
+            if constexpr (WR && !EA1) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool ok = act && b == 0 && e[u] >= 0;
+                    wu[u] = ok ? gbl(re)[ok ? e[u] : 0] : 0.0;
+                }
+            }
+            // the next indices, behind the values in flight
+            if (k + U < d.y) load(nx, d, k + U);
+            else if (j + kWavesPerBlock < gd.w && dn.y > 0) load(nx, dn, 0);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k + u < d.y) {
+                    acc[o[u]] += v[u];
+                    if constexpr (WR)
+                        racc += EA1 ? __shfl(w, u * rows + qc, kWave) : wu[u];
+                }
+        }
         if constexpr (WR) {
             const int rr = j * rows + q;
             const Group lg = load_group(gbl(groups), g);
             if (act && b == 0 && rr < lg.nrows) r[perm[lg.row0 + rr]] = racc;
         }
+        if (d.y == 0 && j + kWavesPerBlock < gd.w && dn.y > 0) load(nx, dn, 0);
+        d = dn;
+        dn = batch(j + 2 * kWavesPerBlock);
     }
     __syncthreads();
     const long base = long(gd.x) * kWave;
     for (int t = threadIdx.x; t < region; t += kBlock) {
-        const double a = acc[t];
-        val[base + t] = a;
+        const double a = acc[lds_place(t)];
+        if constexpr (BIG) __builtin_nontemporal_store(a, val + base + t);
+        else val[base + t] = a;
         if (f32 || bf16) {
             const float f = float(a);
             if (f32) f32[base + t] = f;
@@ -193,24 +276,44 @@ hipError_t launch_assemble_lds(const AsmLdsPlan &P, const double *ke,
                                hipStream_t s)
 {
     if (P.ngroups == 0) return hipSuccess;
-    const size_t lds = size_t(P.region_max + kWave) * sizeof(double);
-    const auto gd = reinterpret_cast<const int4 *>(P.d_gdesc);
-    const auto bd = reinterpret_cast<const int2 *>(P.d_bdesc);
-    if (ordered)
-        hipLaunchKernelGGL((k_assemble_lds<8, false, true>), dim3(P.ngroups),
-                           dim3(kBlock), lds, s, gd, bd, P.d_ea, P.d_off,
-                           P.nde, P.rows, ke, val, f32, bf16, groups, perm,
-                           nullptr, nullptr);
-    else if (re)
-        hipLaunchKernelGGL((k_assemble_lds<8, true, false>), dim3(P.ngroups),
-                           dim3(kBlock), lds, s, gd, bd, P.d_ea, P.d_off,
-                           P.nde, P.rows, ke, val, f32, bf16, groups, perm,
-                           re, r);
-    else
-        hipLaunchKernelGGL((k_assemble_lds<8, false, false>),
-                           dim3(P.ngroups), dim3(kBlock), lds, s, gd, bd,
-                           P.d_ea, P.d_off, P.nde, P.rows, ke, val, f32, bf16,
-                           groups, perm, re, r);
+    const size_t lds = sizeof(double) * (size_t(P.region_max) +
+                                         size_t(P.region_max / kWave) + kWave);
+    auto go = [&](auto wr, auto ord, auto ea1, auto big) {
+        hipLaunchKernelGGL((k_assemble_lds<decltype(wr)::value,
+                                           decltype(ord)::value,
+                                           decltype(ea1)::value,
+                                           decltype(big)::value>),
+                           dim3(P.ngroups), dim3(kBlock), lds, s,
+                           reinterpret_cast<const int4 *>(P.d_gdesc),
+                           reinterpret_cast<const int4 *>(P.d_bdesc), P.d_ea,
+                           reinterpret_cast<const us4 *>(P.d_off), P.nde,
+                           P.rows, ke, val, f32, bf16, groups, perm, re, r);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    auto sized = [&](auto wr, auto ea1) {
+        if (P.big) go(wr, no, ea1, yes);
+        else go(wr, no, ea1, no);
+    };
+    // the element rows of eight steps fit one load of a wavefront
+    const bool ea1 = 8 * P.rows <= kWave;
+    if (ordered) go(no, yes, no, no);
+    else if (re) ea1 ? sized(yes, yes) : sized(yes, no);
+    else ea1 ? sized(no, yes) : sized(no, no);
+    return hipGetLastError();
+}
+
+hipError_t launch_interleave_offsets(const int32_t *bdesc, int64_t nbatch,
+                                     const uint16_t *off, uint16_t *out,
+                                     hipStream_t s)
+{
+    if (nbatch == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_interleave_offsets,
+                       dim3(unsigned((nbatch + kWavesPerBlock - 1) /
+                                     kWavesPerBlock)),
+                       dim3(kBlock), 0, s,
+                       reinterpret_cast<const int4 *>(bdesc), long(nbatch),
+                       off, reinterpret_cast<us4 *>(out));
     return hipGetLastError();
 }
 

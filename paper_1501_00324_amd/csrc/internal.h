@@ -541,15 +541,25 @@ hipError_t launch_assemble(const AsmPlan &P, const double *in, double *out,
 // k-th element row e*nde + a (ascending) and lane q*nde + b adds element
 // value (e*nde + a)*nde + b at its LDS offset.
 constexpr int kAsmLdsMax = 6144;  // doubles of LDS per group region (48 KiB)
+// The last-level cache (256 MB), which smaller element data stays in.
+constexpr int64_t kAsmBig = int64_t(256) << 20;
 struct AsmLdsPlan {
     int32_t ngroups = 0, nde = 0, rows = 0;
     int32_t region_max = 0;      // doubles of the widest group region
+    bool big = false;            // element matrices over kAsmBig bytes
     int64_t nbatch = 0, nrec = 0, contrib = 0;
     int32_t *d_gdesc = nullptr;  // 4 per group: base64, width, batch0, nbatch
-    int32_t *d_bdesc = nullptr;  // 2 per batch: first record, steps
+    int32_t *d_bdesc = nullptr;  // 4 per batch: first record, steps, first
+                                 //   entry of off, 0
     int32_t *d_ea = nullptr;     // `rows` per record: e*nde + a, -1 = none
-    uint16_t *d_off = nullptr;   // 64 per record: LDS offset, 0xffff = none
+    uint16_t *d_off = nullptr;   // LDS offsets (0xffff = none): entries of 64
+                                 //   lanes x 4 steps, a batch's steps rounded
+                                 //   up to a multiple of 4
 };
+// The device form of the offsets, from 64 per record.
+hipError_t launch_interleave_offsets(const int32_t *bdesc, int64_t nbatch,
+                                     const uint16_t *off, uint16_t *out,
+                                     hipStream_t s);
 // With re != NULL the element vectors are summed in the same launch into
 // r (caller numbering: r[perm[layout row]]); groups / perm are the matrix's.
 // With ordered, ke is the plan-ordered element buffer (row rec * rows + q
