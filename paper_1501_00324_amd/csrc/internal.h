@@ -475,7 +475,7 @@ struct WgSys {
     const int32_t *gbase;      // group bases of 16-bit offsets, or NULL
     int32_t n, ngroups, vec, narrow;
     int32_t zl, pad;           // vectors in LDS: 0 none, 1 z = D^-1 r,
-                               // 2 z, x, r, p, q
+                               // 2 z, x, r, p, q; 3 slots in registers
     const int32_t *perm;       // layout row i is caller row perm[i] (NULL:
                                // the same numbering)
     const double *b_in, *x_in; // caller's b and initial guess
@@ -489,6 +489,11 @@ struct WgSys {
 // 64-row chunks per unit (vector step).
 constexpr int32_t kWgGroupsPerUnit = 2;
 constexpr int32_t kWgChunksPerUnit = 4;
+// Slots per lane that a wavefront can hold in registers.
+constexpr int32_t kWgHeldWidth = 8;
+// Threads of the form that holds them (in the place of 1024).
+constexpr int32_t kWgHeldThreads = 768;
+constexpr int32_t kWgUnits = 256;      // compute units
 // threads: 256, 512 or 1024; parts >= every system's group and chunk
 // units (LDS: 48 bytes per part, then vec_doubles for the vectors that the
 // systems keep in LDS: n per system with zl = 1, 5 n with zl = 2).

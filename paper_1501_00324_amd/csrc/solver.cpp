@@ -1334,6 +1334,21 @@ extern "C" fs_status cg_solve_batch_wg(int32_t m, const fs_csr_t *A,
     auto lds_mode = [&](int64_t n, int cap) {
         return std::min(cap, 5 * n <= vcap ? 2 : n <= vcap ? 1 : 0);
     };
+    // slots held in registers (in the place of 1024 threads): one lane per
+    // row, few slots, and all groups in the workgroup's wavefronts, four each
+    auto held = [&](const fs_csr *Ai) {
+        if (Ai->host.groups_by_lanes[0] != Ai->n_groups ||
+            (Ai->n_groups + kWgChunksPerUnit - 1) / kWgChunksPerUnit * kWave >
+                kWgHeldThreads ||
+            lds_mode(Ai->n_rows, 2) != 2)
+            return false;
+        for (const Group &gr : Ai->host.groups)
+            if ((gr.width_lt & 0xffffff) > kWgHeldWidth) return false;
+        return true;
+    };
+    bool all_held = true;
+    for (int32_t i = 0; i < m && all_held; ++i)
+        all_held = A[i]->n_rows == 0 || held(A[i]);
     auto lds_doubles = [&](int cap) {
         int64_t v = 0;
         for (int32_t i = 0; i < m; ++i) {
@@ -1406,26 +1421,35 @@ extern "C" fs_status cg_solve_batch_wg(int32_t m, const fs_csr_t *A,
         // the descriptors with the LDS modes under a cap (uploaded when the
         // stream is idle: before the first launch, and between timed runs)
         int cur_cap = -1;
-        auto modes = [&](int cap) -> fs_status {
-            if (cap == cur_cap) return FS_OK;
+        auto modes = [&](int32_t threads, int cap) -> fs_status {
+            const int key = threads * 4 + cap;
+            if (key == cur_cap) return FS_OK;
             for (int32_t i = 0; i < m; ++i)
-                if (A[i]->n_rows > 0)
-                    hs[size_t(i)].zl = lds_mode(A[i]->n_rows, cap);
+                if (A[i]->n_rows > 0) {
+                    const int md = lds_mode(A[i]->n_rows, cap);
+                    hs[size_t(i)].zl = threads == kWgHeldThreads ? 3 : md;
+                }
             FS_HIP_TRY(hipMemcpyAsync(dsys, hs.data(),
                                       sizeof(WgSys) * size_t(m),
                                       hipMemcpyHostToDevice, s));
-            cur_cap = cap;
+            cur_cap = key;
             return FS_OK;
         };
         auto launch = [&](int32_t threads, int cap, bool write_out)
             -> fs_status {
-            FS_TRY(modes(cap));
+            if (threads == 1024 && cap == 2 && all_held) threads = kWgHeldThreads;
+            FS_TRY(modes(threads, cap));
             FS_HIP_TRY(launch_cg_wg(dsys, m, threads, parts, lds_doubles(cap),
                                     o.rtol, o.maxit, o.x0_zero != 0,
                                     write_out, dev, s));
             return FS_OK;
         };
-        int32_t choice = o.wg_threads ? o.wg_threads * 4 + 2 : 0;
+        // up to one workgroup per compute unit, held slots are the fastest
+        // form (64 systems of 2,116 rows: 140 us against 250 with 1024
+        // threads and 330 with 512); beyond that, more workgroups per unit
+        // with less in LDS can be, which the timed runs tell
+        int32_t choice = o.wg_threads ? o.wg_threads * 4 + 2
+                         : all_held && m <= kWgUnits ? 1024 * 4 + 2 : 0;
         const std::array<int64_t, 6> key = {dev, m, rows, nnz, parts,
                                             int64_t(kinds)};
         if (!choice) {

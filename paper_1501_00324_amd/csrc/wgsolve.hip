@@ -23,6 +23,9 @@
 // rewritten two reductions later, after a barrier that every wavefront
 // reaches only once it has read the region's sums.
 //
+// (The updates are written as explicit fused multiply-adds, so that every
+// form of the kernel rounds alike.)
+//
 // Iteration (as in the persistent solve: the product gathers z, and p and
 // q = A p follow the same recurrence, so the direction update needs no
 // phase of its own; the first iteration takes p = z, q = A z):
@@ -146,7 +149,18 @@ __device__ __forceinline__ void part_totals(const double *buf, int np,
 
 // Where the vectors live (MODE): 0 all in global memory; 1 z in LDS; 2 z,
 // x, r, p and q in LDS (x copied in at the start and out at the end; b and
-// D^-1, which the iterations only read, stay in global memory and L2).
+// D^-1, which the iterations only read, stay in global memory and L2); 3
+// nothing is read from L2 in an iteration: a wavefront holds the slots of
+// its four row groups (one lane per row, up to kHeldWidth slots), p and q in
+// registers, and z, x, r and D^-1 are in LDS.  Four groups are two units of
+// the product step and, with 64 rows each, one of the vector step, so the
+// sums are those of the other modes.  (An iteration waited three times for
+// L2: descriptors, slots, D^-1.  64 systems of 2,116 rows: 7.1 us per
+// iteration in mode 2.)
+constexpr int kHeldWidth = kWgHeldWidth;
+constexpr int kHeldGroups = 4;
+static_assert(kHeldGroups == kCU && kHeldGroups == 2 * kGU,
+              "a wavefront's groups are whole units");
 template <int V, bool N, int MODE>
 __device__ __forceinline__ void wg_solve(const WgSys &S, const WgArgs &a,
                                          double *lds)
@@ -167,8 +181,10 @@ __device__ __forceinline__ void wg_solve(const WgSys &S, const WgArgs &a,
     const bool pc = S.dinv != nullptr;   // Jacobi preconditioner
     // the vectors: LDS after the two part regions (z first), or global
     double *const zl = lds + 6 * P;
+    // (MODE 3: z with a zero after it, which padding slots read)
     auto vec = [&](double *g, int k) {
-        if constexpr (MODE == 2) return zl + long(k) * n;
+        if constexpr (MODE == 3) return zl + long(k) * n + 1;
+        else if constexpr (MODE == 2) return zl + long(k) * n;
         else return gblw(g);
     };
     auto zv = [&]() {
@@ -187,7 +203,7 @@ __device__ __forceinline__ void wg_solve(const WgSys &S, const WgArgs &a,
         else return gbl(static_cast<const double *>(S.z));
     };
     auto xsrc = [&]() {
-        if constexpr (MODE == 2) return static_cast<const double *>(X);
+        if constexpr (MODE >= 2) return static_cast<const double *>(X);
         else return gbl(static_cast<const double *>(S.x));
     };
     int red = 0;   // reductions so far: region (red & 1) is next
@@ -295,11 +311,74 @@ __device__ __forceinline__ void wg_solve(const WgSys &S, const WgArgs &a,
     }
     bool first = true;
     double beta = 0.0;
+    // MODE 3: this wavefront's groups
+    constexpr int HG = MODE == 3 ? kHeldGroups : 1;
+    constexpr int HW = MODE == 3 ? kHeldWidth : 2;
+    double ha[HG][HW], hp[HG], hq[HG];
+    uint32_t hc[HG][HW / 2];             // pairs of columns, n = padding
+    double *const Dl = zl + 3 * long(n) + 1;
+    if constexpr (MODE == 3) {
+#pragma unroll
+        for (int k = 0; k < HG; ++k) {
+            const int g = w * HG + k;
+            hp[k] = hq[k] = 0.0;
+#pragma unroll
+            for (int j = 0; j < HW; ++j) ha[k][j] = 0.0;
+#pragma unroll
+            for (int j = 0; j < HW / 2; ++j) hc[k][j] = uint32_t(n) * 0x10001u;
+            if (g >= ng) continue;
+            const Group gd = group(g);
+            const long base = long(gd.base64) * kWave;
+            const int width = gd.width_lt & 0xffffff;
+#pragma unroll
+            for (int j = 0; j < HW; ++j)
+                if (j < width) {
+                    const long i = base + long(j / V) * kWave * V + lane * V + j % V;
+                    const int c = col[i];
+                    ha[k][j] = val[i];
+                    const uint32_t u = uint32_t(c < 0 ? n : c);
+                    hc[k][j / 2] = j & 1 ? (hc[k][j / 2] & 0xffffu) | (u << 16)
+                                         : (hc[k][j / 2] & 0xffff0000u) | u;
+                }
+        }
+        if (threadIdx.x == 0) zl[n] = 0.0;
+        for (int i = int(threadIdx.x); i < n; i += int(blockDim.x))
+            Dl[i] = pc ? D[i] : 1.0;
+        __syncthreads();
+    }
     while (status == W_RUNNING) {
         // w = A z; p = z + beta p, q = w + beta q; p.q.  The two groups of
         // a unit are multiplied together when their widths agree, and each
         // row's own z, p, q are loaded before the gathers.
         double *buf = region();
+        if constexpr (MODE == 3) {
+            double v[2] = {0.0, 0.0};
+#pragma unroll
+            for (int k = 0; k < HG; ++k) {
+                const int g = w * HG + k, row = g * kWave + lane;
+                if (g >= ng) continue;
+                double zv8[HW];
+#pragma unroll
+                for (int j = 0; j < HW; ++j)
+                    zv8[j] = zl[(hc[k][j / 2] >> (j & 1 ? 16 : 0)) & 0xffffu];
+                const double zi = zl[row < n ? row : n];
+                double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+                for (int j = 0; j < HW; j += 2) {
+                    a0 = fma(ha[k][j], zv8[j], a0);
+                    a1 = fma(ha[k][j + 1], zv8[j + 1], a1);
+                }
+                const double wv = a0 + a1;
+                hp[k] = first ? zi : fma(beta, hp[k], zi);
+                hq[k] = first ? wv : fma(beta, hq[k], wv);
+                if (row < n) v[k / 2] = fma(hp[k], hq[k], v[k / 2]);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const double t = wave_sum(v[u]);
+                if (lane == 0 && w * 2 + u < nug) buf[w * 2 + u] = t;
+            }
+        } else
         for (int u = w; u < nug; u += nw) {
             const int g0 = u * kGU, g1 = g0 + 1;
             const bool two = g1 < ng;
@@ -327,18 +406,18 @@ __device__ __forceinline__ void wg_solve(const WgSys &S, const WgArgs &a,
             }
             double v = 0.0;
             if (own0) {
-                const double pi = first ? z0 : z0 + beta * p0;
-                const double qi = first ? w0 : w0 + beta * q0;
+                const double pi = first ? z0 : fma(beta, p0, z0);
+                const double qi = first ? w0 : fma(beta, q0, w0);
                 Pv[row0] = pi;
                 Q[row0] = qi;
-                v += pi * qi;
+                v = fma(pi, qi, v);
             }
             if (own1) {
-                const double pi = first ? z1 : z1 + beta * p1;
-                const double qi = first ? w1 : w1 + beta * q1;
+                const double pi = first ? z1 : fma(beta, p1, z1);
+                const double qi = first ? w1 : fma(beta, q1, w1);
                 Pv[row1] = pi;
                 Q[row1] = qi;
-                v += pi * qi;
+                v = fma(pi, qi, v);
             }
             v = wave_sum(v);
             if (lane == 0) buf[u] = v;
@@ -363,23 +442,29 @@ __device__ __forceinline__ void wg_solve(const WgSys &S, const WgArgs &a,
                 const int i = (u * kCU + k) * kWave + lane;
                 const int ic = i < n ? i : 0;
                 rv[k] = R[ic];
-                qv[k] = Q[ic];
                 xv[k] = X[ic];
-                pv[k] = Pv[ic];
-                dv[k] = pc ? D[ic] : 1.0;
+                if constexpr (MODE == 3) {
+                    qv[k] = hq[k];
+                    pv[k] = hp[k];
+                    dv[k] = Dl[ic];
+                } else {
+                    qv[k] = Q[ic];
+                    pv[k] = Pv[ic];
+                    dv[k] = pc ? D[ic] : 1.0;
+                }
             }
             double v0 = 0.0, v1 = 0.0;
 #pragma unroll
             for (int k = 0; k < kCU; ++k) {
                 const int i = (u * kCU + k) * kWave + lane;
                 if (i < n) {
-                    const double ri = rv[k] - alpha * qv[k];
-                    X[i] = xv[k] + alpha * pv[k];
+                    const double ri = fma(-alpha, qv[k], rv[k]);
+                    X[i] = fma(alpha, pv[k], xv[k]);
                     R[i] = ri;
                     const double zi = pc ? dv[k] * ri : ri;
                     zput(i, zi);
-                    v0 += ri * zi;
-                    v1 += ri * ri;
+                    v0 = fma(ri, zi, v0);
+                    v1 = fma(ri, ri, v1);
                 }
             }
             v0 = wave_sum(v0);
@@ -475,6 +560,19 @@ __device__ __forceinline__ void wg_solve(const WgSys &S, const WgArgs &a,
     }
 }
 
+template <int M>
+__device__ __forceinline__ void wg_by_stream(const WgSys &S, const WgArgs &a,
+                                             double *lds)
+{
+    if (S.vec == 2) {
+        if (S.narrow) wg_solve<2, true, M>(S, a, lds);
+        else wg_solve<2, false, M>(S, a, lds);
+    } else {
+        if (S.narrow) wg_solve<1, true, M>(S, a, lds);
+        else wg_solve<1, false, M>(S, a, lds);
+    }
+}
+
 template <int BS>
 __global__ __launch_bounds__(BS) void k_cg_wg(const WgSys *__restrict__ sys,
                                               const WgArgs a)
@@ -482,19 +580,20 @@ __global__ __launch_bounds__(BS) void k_cg_wg(const WgSys *__restrict__ sys,
     extern __shared__ double lds[];
     const WgSys S = sys[blockIdx.x];
     if (S.n == 0) return;
-    auto go = [&](auto mode) {
-        constexpr int M = decltype(mode)::value;
-        if (S.vec == 2) {
-            if (S.narrow) wg_solve<2, true, M>(S, a, lds);
-            else wg_solve<2, false, M>(S, a, lds);
-        } else {
-            if (S.narrow) wg_solve<1, true, M>(S, a, lds);
-            else wg_solve<1, false, M>(S, a, lds);
-        }
-    };
-    if (S.zl == 2) go(std::integral_constant<int, 2>());
-    else if (S.zl == 1) go(std::integral_constant<int, 1>());
-    else go(std::integral_constant<int, 0>());
+    if (S.zl == 2) wg_by_stream<2>(S, a, lds);
+    else if (S.zl == 1) wg_by_stream<1>(S, a, lds);
+    else wg_by_stream<0>(S, a, lds);
+}
+
+// Every system in mode 3: 12 wavefronts, whose 168 registers hold four
+// groups (1024 threads leave 128, which spill them).
+__global__ __launch_bounds__(kWgHeldThreads) void k_cg_wg_held(
+    const WgSys *__restrict__ sys, const WgArgs a)
+{
+    extern __shared__ double lds[];
+    const WgSys S = sys[blockIdx.x];
+    if (S.n == 0) return;
+    wg_by_stream<3>(S, a, lds);
 }
 
 }  // namespace
@@ -516,7 +615,9 @@ hipError_t launch_cg_wg(const WgSys *d_sys, int32_t m, int32_t threads,
     a.write_out = write_out ? 1 : 0;
     a.parts = parts;
     const size_t lds = sizeof(double) * size_t(2 * 3 * parts + vec_doubles);
-    const void *fn = threads == 256   ? reinterpret_cast<const void *>(k_cg_wg<256>)
+    const void *fn = threads == kWgHeldThreads
+                         ? reinterpret_cast<const void *>(k_cg_wg_held)
+                     : threads == 256 ? reinterpret_cast<const void *>(k_cg_wg<256>)
                      : threads == 512 ? reinterpret_cast<const void *>(k_cg_wg<512>)
                      : threads == 1024
                          ? reinterpret_cast<const void *>(k_cg_wg<1024>)
@@ -529,6 +630,10 @@ hipError_t launch_cg_wg(const WgSys *d_sys, int32_t m, int32_t threads,
         if (e != hipSuccess) return e;
     }
     switch (threads) {
+    case kWgHeldThreads:
+        hipLaunchKernelGGL(k_cg_wg_held, dim3(m), dim3(kWgHeldThreads), lds, s,
+                           d_sys, a);
+        break;
     case 256:
         hipLaunchKernelGGL(k_cg_wg<256>, dim3(m), dim3(256), lds, s, d_sys, a);
         break;
