@@ -104,6 +104,13 @@ fs_status build_refresh_rows(fs_csr *A, const int32_t *h_rp, int64_t &acct,
     if (maxlen > 255) return FS_OK;
     FS_TRY(dalloc(&A->d_jpos, A->slots, acct));
     FS_TRY(dalloc(&A->d_rstart, A->n_rows, acct));
+    for (const Group &g : A->host.groups) {
+        A->refresh_width = std::max(A->refresh_width, g.width_lt & 0xffffff);
+        if ((g.width_lt >> 24) > 4 || A->refresh_width > kRefreshWidth) {
+            A->refresh_width = 0;
+            break;
+        }
+    }
     FS_HIP_TRY(launch_refresh_rows(A->d_groups, A->n_groups, A->host.vec,
                                    A->d_imap, A->d_jpos, A->d_rstart, s));
     return FS_OK;
@@ -770,8 +777,8 @@ fs_status csr_update_values(fs_csr_t A, const double *vals, hipStream_t s)
     DeviceGuard g(A->device);
     if (A->d_jpos)
         FS_HIP_TRY(launch_value_refresh_rows(
-            A->d_groups, A->n_groups, A->host.vec, A->d_jpos, A->d_rstart,
-            vals, A->d_val, A->d_val_f32, A->d_val_bf16, s));
+            A->d_groups, A->n_groups, A->host.vec, A->refresh_width, A->nnz,
+            A->d_jpos, A->d_rstart, vals, A->d_val, A->d_val_f32, A->d_val_bf16, s));
     else
         FS_HIP_TRY(launch_value_refresh(A->d_groups, A->n_groups, A->d_imap,
                                         vals, A->d_val, A->d_val_f32,

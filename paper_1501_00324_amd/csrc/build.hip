@@ -8,6 +8,8 @@
 // Paper: section "Cost of Reordering Matrix Values" -- the layout's value
 // map comes from one scan of the pattern, after which every value refresh is
 // a device scatter; here that scan runs on the device as well.
+#include <type_traits>
+
 #include "device.h"
 
 namespace fs {
@@ -493,6 +495,102 @@ __global__ __launch_bounds__(kBlock) void k_value_refresh_rows(
     }
 }
 
+// The same with the CSR rows read along their length: a wavefront takes 16
+// lanes of a group (16 / T rows), copies the T * width values from each row
+// start into LDS with consecutive lanes on consecutive values, and its
+// slots pick theirs from there.  The direct form gathers 64 rows' values with
+// every load, each from a line of its own, which leave the L1 before their
+// 16 values are used: P1 elasticity 64^3 in random numbering with an FP32
+// copy 210 us, this form 148 us = 4.9 TB/s (the copy rate); rows in CSR order
+// (Q1 elasticity 60^3 with a BF16 copy) 186 against 188 us.  Loading the
+// positions ahead of the rows: 6 us slower.  A row shorter than T * width
+// reads on into the next rows' values (clamped to the array), which no slot
+// picks.  Needs T <= 16 and 16 * width doubles of LDS per wavefront.
+template <int V>
+__global__ __launch_bounds__(kBlock) void k_value_refresh_tiles(
+    const Group *__restrict__ groups, const uint8_t *__restrict__ jpos,
+    const int *__restrict__ rstart, const double *__restrict__ vals, long nnz,
+    int lds_wave, double *__restrict__ val, float *__restrict__ f32,
+    uint16_t *__restrict__ bf16)
+{
+    // positions of V slots (in byte order)
+    typedef typename std::conditional<V == 1, uint8_t, uint16_t>::type J;
+    typedef typename Slots<V>::D D;
+    extern __shared__ double rows_[];
+    const int g = xcd_remap(blockIdx.x, gridDim.x);
+    const Group G = load_group(gbl(groups), g);
+    const int w = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int lane = threadIdx.x & (kWave - 1);
+    const int lt = G.width_lt >> 24, width = G.width_lt & 0xffffff;
+    const int len = width << lt, nr = 16 >> lt;      // row length, rows
+    const int row0 = w * nr;                         // in the group
+    const int have = min(nr, G.nrows - row0);        // rows that exist
+    double *const t = rows_ + w * lds_wave;
+    // lane r (< nr) knows row r's start
+    const int mine = lane < have ? rstart[G.row0 + row0 + lane] : 0;
+    const int total = max(have, 0) * len;
+    const float inv = 1.0f / float(len);
+    const long base = long(G.base64) * kWave;
+    const int nch = width / V, l = lane & 15;
+    const auto pj = gbl(reinterpret_cast<const J *>(jpos + base)) + w * 16 + l;
+    constexpr int U = 12;
+    for (int i0 = 0; i0 < total; i0 += U * kWave) {
+        double a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kWave + lane;
+            // i / len exactly: both at most 16 * 64
+            const int ic = min(i, total - 1);
+            const int r = int((float(ic) + 0.5f) * inv), j = ic - r * len;
+            const long at = long(__shfl(mine, r, kWave)) + j;
+            if (i0 + u * kWave < total) a[u] = gbl(vals)[at < nnz ? at : nnz - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * kWave + lane;
+            if (i < total) t[i] = a[u];
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    // slots: V of 16 lanes in four chunks per step
+    const int r = l >> lt;
+    const bool real = r < have;
+    const int tr = (real ? r : 0) * len;
+    auto pick = [&](int jp) { return real && jp != 255 ? t[tr + jp] : 0.0; };
+    auto step = [&](int s, J jp) {
+        const int c = 4 * s + (lane >> 4);
+        if (c >= nch) return;
+        const long at = base / V + long(c) * kWave + w * 16 + l;
+        D v;
+        if constexpr (V == 1) {
+            v = pick(jp);
+        } else {
+            v.x = pick(jp & 0xff);
+            v.y = pick(jp >> 8);
+        }
+        __builtin_nontemporal_store(v, reinterpret_cast<D *>(val) + at);
+        if (!f32 && !bf16) return;
+        if constexpr (V == 1) {
+            const float f = float(v);
+            if (f32) __builtin_nontemporal_store(f, f32 + at);
+            if (bf16) __builtin_nontemporal_store(f32_to_bf16_rne(f), bf16 + at);
+        } else {
+            fv2 f;
+            f.x = float(v.x);
+            f.y = float(v.y);
+            us2 h;
+            h.x = f32_to_bf16_rne(f.x);
+            h.y = f32_to_bf16_rne(f.y);
+            if (f32) __builtin_nontemporal_store(f, reinterpret_cast<fv2 *>(f32) + at);
+            if (bf16) __builtin_nontemporal_store(h, reinterpret_cast<us2 *>(bf16) + at);
+        }
+    };
+    for (int s = 0; 4 * s < nch; ++s)
+        step(s, pj[long(min(4 * s + (lane >> 4), nch - 1)) * kWave]);
+}
+
 int wave_grid(long waves)
 {
     const long b = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -534,13 +632,28 @@ hipError_t launch_refresh_rows(const Group *groups, int32_t ngroups,
 }
 
 hipError_t launch_value_refresh_rows(const Group *groups, int32_t ngroups,
-                                     int32_t vec, const uint8_t *jpos,
+                                     int32_t vec, int32_t tile_width,
+                                     int64_t nnz, const uint8_t *jpos,
                                      const int32_t *rstart,
                                      const double *vals, double *val,
                                      float *f32, uint16_t *bf16,
                                      hipStream_t s)
 {
     if (ngroups == 0) return hipSuccess;
+    if (tile_width > 0) {
+        // an odd stride between the wavefronts' tiles (banks)
+        const int per = 16 * tile_width + 1;
+        const size_t lds = sizeof(double) * size_t(per) * kWavesPerBlock;
+        if (vec == 1)
+            hipLaunchKernelGGL(k_value_refresh_tiles<1>, dim3(ngroups),
+                               dim3(kBlock), lds, s, groups, jpos, rstart,
+                               vals, long(nnz), per, val, f32, bf16);
+        else
+            hipLaunchKernelGGL(k_value_refresh_tiles<2>, dim3(ngroups),
+                               dim3(kBlock), lds, s, groups, jpos, rstart,
+                               vals, long(nnz), per, val, f32, bf16);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_value_refresh_rows, dim3(ngroups), dim3(kBlock), 0,
                        s, groups, vec, jpos, rstart, vals, val, f32, bf16);
     return hipGetLastError();

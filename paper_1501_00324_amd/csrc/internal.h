@@ -103,6 +103,9 @@ struct StageArgs {
 // many of them per slot, over the matrix, the staging pays for.
 constexpr int32_t kStageMax = 1280;
 constexpr double kStageMost = 0.45;
+// Most slots per lane of a group whose rows the value refresh stages (32 KB
+// of LDS per workgroup).
+constexpr int32_t kRefreshWidth = 64;
 // Rows per pattern, over the matrix, from which the multi-column products run
 // on the matrix cores (a pattern is a tile of up to four rows).
 constexpr double kTileRows = 2.0;
@@ -338,6 +341,9 @@ struct fs_csr {
     // position within the row, 255 = padding; NULL: refresh through d_imap
     uint8_t *d_jpos = nullptr;
     int32_t *d_rstart = nullptr;
+    // the refresh stages rows in LDS: slots per lane of the widest group, 0:
+    // it gathers them (more than 16 lanes per row, or over kRefreshWidth)
+    int32_t refresh_width = 0;
     int32_t *d_perm = nullptr;
     int32_t *d_iperm = nullptr;
     double *d_xtmp = nullptr;      // gathered x for caller-numbering spmv
@@ -389,9 +395,11 @@ hipError_t launch_value_refresh(const Group *groups, int32_t ngroups,
 hipError_t launch_refresh_rows(const Group *groups, int32_t ngroups,
                                int32_t vec, const int32_t *imap,
                                uint8_t *jpos, int32_t *rstart, hipStream_t s);
-// the refresh through them
+// the refresh through them; tile_width > 0: the widest group's slots per
+// lane, rows are staged in LDS
 hipError_t launch_value_refresh_rows(const Group *groups, int32_t ngroups,
-                                     int32_t vec, const uint8_t *jpos,
+                                     int32_t vec, int32_t tile_width,
+                                     int64_t nnz, const uint8_t *jpos,
                                      const int32_t *rstart,
                                      const double *vals, double *val,
                                      float *f32, uint16_t *bf16,

@@ -128,3 +128,25 @@ def test_tile_padding_and_infinity(k):
         hit = np.zeros((A.n_rows, k), bool)
         hit[rows[A.col == j], c] = True
         assert np.array_equal(~np.isfinite(host(fs.spmm(M, dev(X)))), hit)
+
+
+@pytest.mark.parametrize("vec", [1, 2])
+@pytest.mark.parametrize("lanes", [0, 2, 8, 16, 32])
+@pytest.mark.parametrize("name", ["three", "lanes", "empty", "single", "one row", "wide"])
+def test_refresh_rows_in_lds(name, lanes, vec):
+    """New values land in their slots whatever the lanes per row (over 16 the
+    rows are gathered), unsorted rows included: bitwise a fresh handle."""
+    note("refresh %s lanes=%d vec=%d" % (name, lanes, vec))
+    A = block_matrix(seed=17, **CASES[name])
+    opts = dict(vec=vec, lanes_min=lanes, lanes_max=lanes, dtypes=fs.DT_F32 | fs.DT_BF16)
+    new = np.random.default_rng(18).uniform(-1, 1, A.nnz)
+    M = make(A, **opts)
+    fs.csr_update_values(M, dev(new))
+    F = make(CSR(A.n_rows, A.n_cols, A.rowptr, A.col, new), **opts)
+    assert np.array_equal(host(fs.csr_get_values(M)), new)
+    x = dev(np.random.default_rng(19).uniform(-1, 1, A.n_cols))
+    assert np.array_equal(host(fs.spmv(M, x)), host(fs.spmv(F, x)))
+    if A.n_rows == A.n_cols:
+        for d in (fs.DT_F32, fs.DT_BF16):
+            assert np.array_equal(host(fs.spmv_lowp(M, d, x.float())),
+                                  host(fs.spmv_lowp(F, d, x.float())))
