@@ -1239,20 +1239,26 @@ __global__ void k_gather_states(const SysDesc *__restrict__ sys,
 }
 
 // Row permutation of an n x k block: TO_LAYOUT dst[i, :] = src[perm[i], :],
-// else dst[perm[i], :] = src[i, :].  ld of the caller side is ldc, of the
-// layout side k.
-template <bool TO_LAYOUT>
+// else dst[perm[i], :] = src[i, :].  W values per thread; kw = k / W, and
+// W = 2 needs even k and strides, and 16-byte aligned blocks (774,144 rows of
+// 16: 36 us = 5.6 TB/s, 48 us by single values with a 64-bit division each).
+template <bool TO_LAYOUT, int W>
 __global__ __launch_bounds__(kBlock) void k_permute_rows(
-    int n, int k, const int *__restrict__ perm, const double *__restrict__ src,
-    long lds, double *__restrict__ dst, long ldd)
+    long n, unsigned kw, const int *__restrict__ perm,
+    const double *__restrict__ src, long lds, double *__restrict__ dst,
+    long ldd)
 {
-    const long total = long(n) * k;
+    typedef typename std::conditional<W == 1, double, dv2>::type T;
+    const long total = n * kw;
     for (long e = long(blockIdx.x) * kBlock + threadIdx.x; e < total;
          e += long(gridDim.x) * kBlock) {
-        const int i = int(e / k), c = int(e % k);
+        // most blocks fit a 32-bit division
+        const long i = total <= 0xffffffffL ? long(unsigned(e) / kw) : e / long(kw);
+        const long c = (e - i * long(kw)) * W;
         const long pi = perm ? perm[i] : i;
-        if (TO_LAYOUT) dst[i * ldd + c] = src[pi * lds + c];
-        else dst[pi * ldd + c] = src[i * lds + c];
+        const long s = (TO_LAYOUT ? pi : i) * lds + c;
+        const long d = (TO_LAYOUT ? i : pi) * ldd + c;
+        *reinterpret_cast<T *>(dst + d) = *reinterpret_cast<const T *>(src + s);
     }
 }
 
@@ -1381,14 +1387,22 @@ hipError_t permute_rows(int32_t n, int32_t k, const int32_t *perm,
 {
     const long total = long(n) * k;
     if (total == 0) return hipSuccess;
-    if (to_layout)
-        hipLaunchKernelGGL(k_permute_rows<true>, dim3(flat_blocks(total)),
-                           dim3(kBlock), 0, s, n, k, perm, src, long(lds), dst,
+    const bool pairs = k % 2 == 0 && lds % 2 == 0 && ldd % 2 == 0 &&
+                       reinterpret_cast<uintptr_t>(src) % 16 == 0 &&
+                       reinterpret_cast<uintptr_t>(dst) % 16 == 0;
+    auto go = [&](auto to, auto w) {
+        constexpr int W = decltype(w)::value;
+        hipLaunchKernelGGL((k_permute_rows<decltype(to)::value, W>),
+                           dim3(flat_blocks(total / W)), dim3(kBlock), 0, s,
+                           long(n), unsigned(k / W), perm, src, long(lds), dst,
                            long(ldd));
-    else
-        hipLaunchKernelGGL(k_permute_rows<false>, dim3(flat_blocks(total)),
-                           dim3(kBlock), 0, s, n, k, perm, src, long(lds), dst,
-                           long(ldd));
+    };
+    auto by_width = [&](auto to) {
+        if (pairs) go(to, std::integral_constant<int, 2>());
+        else go(to, std::integral_constant<int, 1>());
+    };
+    if (to_layout) by_width(std::true_type());
+    else by_width(std::false_type());
     return hipGetLastError();
 }
 
