@@ -112,11 +112,13 @@ __global__ __launch_bounds__(kBlock) void k_interleave_offsets(
 // What bounds it is the address unit (four lanes a cycle, whatever they
 // load) and one chain of loads -- index, then value -- per eight steps.  So
 // a lane's LDS offsets come four steps to a load, the element rows of eight
-// steps (8 rows <= 64 of them, EA1) as one load of which every lane takes
+// steps (8 rows <= 64 of them, EL = 1) as one load of which every lane takes
 // its steps by shuffles, their vector entries likewise; and the indices of
 // the next eight steps are in flight while the values of these are waited
 // for.  12 (11 without the vector) load instructions per eight steps instead
-// of 32 (24).  Steps past a batch's last one are skipped, lanes without work
+// of 32 (24).  Elements of four to seven unknowns, whose batches hold up to
+// 16 rows, take two loads (EL) of element rows per eight steps; smaller ones
+// load every step's lane by lane (EL = 0), four steps at a time.  Steps past a batch's last one are skipped, lanes without work
 // add 0.0 into a private dummy slot past the group region.  With ORD the
 // element rows come from a buffer stored in the plan's own order (row
 // rec * rows + q), so they are read contiguously and ea is not needed.
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void k_interleave_offsets(
 // groups side by side, and the values stream out past the caches.  Smaller
 // data keeps the contiguous ranges (P1 Laplacian 70^3, 252 MB: 203 us, 218
 // in chunks).
-template <bool WR, bool ORD, bool EA1, bool BIG>
+template <int U, bool WR, bool ORD, int EL, bool BIG>
 __global__ __launch_bounds__(kBlock) void k_assemble_lds(
     const int4 *__restrict__ gdesc, const int4 *__restrict__ bdesc,
     const int *__restrict__ ea, const us4 *__restrict__ off, int nde,
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(kBlock) void k_assemble_lds(
     const Group *__restrict__ groups, const int *__restrict__ perm,
     const double *__restrict__ re, double *__restrict__ r)
 {
-    constexpr int U = 8;
+    static_assert(U == 4 || U == 8, "offsets come four steps to a load");
     extern __shared__ double acc[];   // group region + 64 dummy slots
     int g;
     if constexpr (BIG) {
@@ -161,10 +163,12 @@ __global__ __launch_bounds__(kBlock) void k_assemble_lds(
     const auto pe = gbl(ea);
     const auto po = gbl(off);
     const auto pk = gbl(ke);
-    // indices of the eight steps from k of batch d
+    // indices of the U steps from k of batch d
+    constexpr bool EA1 = EL > 0;
+    constexpr int UL = EA1 ? U / EL : U;   // steps per load of element rows
     struct Index {
-        us4 o[2];
-        int e[EA1 ? 1 : U];
+        us4 o[U / 4];
+        int e[EA1 ? EL : U];
     };
     auto batch = [&](int j) {
         const int4 d = bdesc[gd.z + min(j, gd.w - 1)];
@@ -175,11 +179,16 @@ __global__ __launch_bounds__(kBlock) void k_assemble_lds(
     auto load = [&](Index &x, const int4 &d, int k) {
         const auto p = po + (long(d.z) + (k >> 2)) * kWave + lane;
         x.o[0] = __builtin_nontemporal_load(p);
-        if (k + 4 < d.y) x.o[1] = __builtin_nontemporal_load(p + kWave);
+        if constexpr (U == 8) {
+            if (k + 4 < d.y) x.o[1] = __builtin_nontemporal_load(p + kWave);
+        }
         if constexpr (!ORD && EA1) {
             // lane u * rows + q: step u of row q (past the batch: its last)
-            const int i = min(k * rows + lane, d.y * rows - 1);
-            x.e[0] = __builtin_nontemporal_load(pe + long(d.x) * rows + i);
+#pragma unroll
+            for (int l = 0; l < EL; ++l) {
+                const int i = min((k + l * UL) * rows + lane, d.y * rows - 1);
+                x.e[l] = __builtin_nontemporal_load(pe + long(d.x) * rows + i);
+            }
         } else if constexpr (!ORD) {
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -197,33 +206,44 @@ __global__ __launch_bounds__(kBlock) void k_assemble_lds(
         for (int k = 0; k < d.y; k += U) {
             const Index x = nx;
             int o[U], e[U];
-            double v[U], w = 0.0;
+            double v[U], w[EA1 ? EL : 1];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 o[u] = x.o[u >> 2][u & 3];
                 if (u >= 4 && k + 4 >= d.y) o[u] = 0xffff;
                 if constexpr (ORD) e[u] = 0;
-                else if constexpr (EA1) e[u] = __shfl(x.e[0], u * rows + qc, kWave);
+                else if constexpr (EA1) e[u] = __shfl(x.e[u / UL], (u % UL) * rows + qc, kWave);
                 else e[u] = k + u < d.y ? x.e[u] : -1;
             }
             if constexpr (WR && EA1) {
-                const bool ok = lane < U * rows && x.e[0] >= 0;
-                w = ok ? gbl(re)[x.e[0]] : 0.0;
-            }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                v[u] = 0.0;
-                if (k + u >= d.y) continue;
-                const bool use = act && o[u] != 0xffff && (ORD || e[u] >= 0);
-                if constexpr (ORD) {
-                    // rows of dropped element rows carry offsets 0xffff only
+                for (int l = 0; l < EL; ++l) {
+                    const bool ok = lane < UL * rows && x.e[l] >= 0;
+                    w[l] = gbl(re)[ok ? x.e[l] : 0];
+                    w[l] = ok ? w[l] : 0.0;
+                }
+            }
+            bool use[U];
+            auto value = [&](int u) {
+                use[u] = act && o[u] != 0xffff && (ORD || e[u] >= 0);
+                // (rows of dropped element rows carry offsets 0xffff only)
+                if constexpr (ORD)
                     v[u] = __builtin_nontemporal_load(
                         pk + ((long(d.x) + k + u) * rows + qc) * nde + b);
-                } else {
-                    v[u] = pk[long(use ? e[u] : 0) * nde + b];
+                else
+                    v[u] = pk[long(use[u] ? e[u] : 0) * nde + b];
+            };
+            // all loads before the first use: a whole block has no branches
+            if (k + U <= d.y) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) value(u);
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    use[u] = false;
+                    v[u] = 0.0;
+                    if (k + u < d.y) value(u);
                 }
-                v[u] = use ? v[u] : 0.0;
-                o[u] = use ? o[u] : dummy;
             }
             double wu[U];
             if constexpr (WR && !EA1) {
@@ -236,13 +256,19 @@ __global__ __launch_bounds__(kBlock) void k_assemble_lds(
             // the next indices, behind the values in flight
             if (k + U < d.y) load(nx, d, k + U);
             else if (j + kWavesPerBlock < gd.w && dn.y > 0) load(nx, dn, 0);
+            if constexpr (WR && EA1) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    wu[u] = __shfl(w[u / UL], (u % UL) * rows + qc, kWave);
+            }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (k + u < d.y) {
-                    acc[o[u]] += v[u];
-                    if constexpr (WR)
-                        racc += EA1 ? __shfl(w, u * rows + qc, kWave) : wu[u];
-                }
+                acc[use[u] ? o[u] : dummy] += use[u] ? v[u] : 0.0;
+            if constexpr (WR) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (k + u < d.y) racc += wu[u];
+            }
         }
         if constexpr (WR) {
             const int rr = j * rows + q;
@@ -278,10 +304,11 @@ hipError_t launch_assemble_lds(const AsmLdsPlan &P, const double *ke,
     if (P.ngroups == 0) return hipSuccess;
     const size_t lds = sizeof(double) * (size_t(P.region_max) +
                                          size_t(P.region_max / kWave) + kWave);
-    auto go = [&](auto wr, auto ord, auto ea1, auto big) {
-        hipLaunchKernelGGL((k_assemble_lds<decltype(wr)::value,
+    auto go = [&](auto u, auto wr, auto ord, auto el, auto big) {
+        hipLaunchKernelGGL((k_assemble_lds<decltype(u)::value,
+                                           decltype(wr)::value,
                                            decltype(ord)::value,
-                                           decltype(ea1)::value,
+                                           decltype(el)::value,
                                            decltype(big)::value>),
                            dim3(P.ngroups), dim3(kBlock), lds, s,
                            reinterpret_cast<const int4 *>(P.d_gdesc),
@@ -291,15 +318,23 @@ hipError_t launch_assemble_lds(const AsmLdsPlan &P, const double *ke,
     };
     const std::true_type yes;
     const std::false_type no;
-    auto sized = [&](auto wr, auto ea1) {
-        if (P.big) go(wr, no, ea1, yes);
-        else go(wr, no, ea1, no);
+    const std::integral_constant<int, 8> eight;
+    const std::integral_constant<int, 4> four;
+    const std::integral_constant<int, 0> none;
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    auto sized = [&](auto u, auto wr, auto el) {
+        if (P.big) go(u, wr, no, el, yes);
+        else go(u, wr, no, el, no);
     };
-    // the element rows of eight steps fit one load of a wavefront
-    const bool ea1 = 8 * P.rows <= kWave;
-    if (ordered) go(no, yes, no, no);
-    else if (re) ea1 ? sized(yes, yes) : sized(yes, no);
-    else ea1 ? sized(no, yes) : sized(no, no);
+    auto stepped = [&](auto wr) {
+        if (8 * P.rows <= kWave) sized(eight, wr, one);
+        else if (4 * P.rows <= kWave) sized(eight, wr, two);
+        else sized(four, wr, none);
+    };
+    if (ordered) go(eight, no, yes, none, no);
+    else if (re) stepped(yes);
+    else stepped(no);
     return hipGetLastError();
 }
 
