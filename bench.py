@@ -928,7 +928,7 @@ def main():
                          "dram_gbs": (round(traffic / (us * 1e-6) / 1e9, 1)
                                       if traffic else None),
                          "bytes_algorithmic": bytes_alg,
-                         "kernel": "k_spmv_f64",
+                         "kernel": "k_spmv_staged",
                          "cold_frac": round(prod["cold_gbs"] /
                                             HBM_PEAK_GBS, 4)},
             "paper_model_gbs": round(20 * h_nnz / (us * 1e-6) / 1e9, 2),

@@ -8,7 +8,11 @@
 //    so each wave-wide access is one contiguous 1 KiB (values) / 512 B
 //    (columns) block; the matrix stream is loaded non-temporally so that the
 //    gathered vector keeps its place in L2 / MALL;
-//  * rows with T > 1 lanes are reduced with cross-lane shuffles (no LDS
+//  * a wavefront copies the entries of x its row group references into LDS
+//    once and its slots read them there (k_spmv_staged, device.h); the
+//    kernels below gather per slot, for matrices whose groups reference too
+//    many columns for that;
+//  * rows with T > 1 lanes are reduced with cross-lane moves (no LDS
 //    traffic, no barrier), replacing the paper's shared-memory tree;
 //  * workgroups are renumbered so that each of the 8 XCDs (own 4 MB L2)
 //    walks a contiguous range of row groups and therefore a narrow window
