@@ -1095,14 +1095,18 @@ int32_t engine_vec_blocks(int32_t n, int32_t k)
 }
 
 // f(true_type) when the launch's products are staged (one column) or run on
-// the matrix cores (4 or more columns, FP64).
+// the matrix cores (classes of 4 and 8 columns, FP64).  With 16 columns the
+// pairs of coop_group_pair are faster here: a solve of the P1 elasticity step
+// takes 15.9 ms with them and 17.3 on the matrix cores (64^3 nodes; 4.3 and
+// 4.5 ms at 36^3), whose two work items per group and three wavefronts per
+// SIMD leave the dot products' reads of P exposed.
 template <typename ST, int KM, class F>
 static void with_stage(const EngineLaunch &L, F &&f)
 {
     if constexpr (KM == 1) {
         if (L.stage) return f(std::true_type());
     }
-    if constexpr (KM >= 4 && std::is_same<ST, double>::value) {
+    if constexpr ((KM == 4 || KM == 8) && std::is_same<ST, double>::value) {
         if (L.tiles) return f(std::true_type());
     }
     f(std::false_type());
