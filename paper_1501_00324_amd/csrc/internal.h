@@ -159,8 +159,8 @@ struct SysDesc {
 
 // Column-count class of a system with k right-hand sides: the launch's
 // compile-time column count (1, 2, 4, 8 or 16) and its index 0..4.  Systems
-// share a launch only with systems of the same class, so the arithmetic of
-// a system never depends on the other members of its batch.
+// share a launch only with systems of the same solve_class, so the
+// arithmetic of a system never depends on the other members of its batch.
 constexpr int kKmClasses = 5;
 inline int32_t km_for(int32_t k)
 {
@@ -378,6 +378,26 @@ inline StageArgs stage_of(const fs_csr *A)
 {
     return {A->d_sgrp, A->d_loc, A->d_lpat, A->d_scols, A->d_gbase};
 }
+
+// Whether a solve of k columns takes its products on the matrix cores: the
+// classes of 4 and 8 columns (engine.hip: with_stage), vectors within the
+// 31-bit offsets of tiles.h.
+inline bool runs_tiles(const fs_csr *A, int32_t k)
+{
+    return (km_for(k) == 4 || km_for(k) == 8) && A->row_tiles &&
+           int64_t(A->n_rows) * k < (int64_t(1) << 28) - 16;
+}
+
+// Launch class of a solve: its product's form, slots per load and column
+// count.  The tiles add a row's entries in another order than the other
+// form, so a launch holds systems of one of them only.
+constexpr int kSolveClasses = 4 * kKmClasses;
+inline int32_t solve_class(const fs_csr *A, int32_t k)
+{
+    return (2 * int32_t(runs_tiles(A, k)) + A->host.vec - 1) * kKmClasses +
+           km_index(k);
+}
+inline int32_t class_vec(int32_t cls) { return 1 + cls / kKmClasses % 2; }
 
 // ---------------------------------------------------------------- launchers
 // All launchers are asynchronous on stream s and return hipError_t.

@@ -104,8 +104,8 @@ struct fs_server {
     int64_t peak_used = 0;
     int32_t peak_active = 0;
     // running members per slot width and column-count class; joiners
-    fs::Batch batch[2 * fs::kKmClasses], join[2 * fs::kKmClasses];
-    int32_t stable[2 * fs::kKmClasses] = {};   // steps without a change
+    fs::Batch batch[fs::kSolveClasses], join[fs::kSolveClasses];
+    int32_t stable[fs::kSolveClasses] = {};   // steps without a change
     // free device blocks by size class (worker thread only)
     std::multimap<int64_t, void *> pool;
     int64_t pool_bytes = 0;                    // all blocks, free or in use
@@ -122,7 +122,7 @@ hipStream_t class_stream(const fs_server *S, int32_t cls)
 
 int32_t class_of(const Request *R)
 {
-    return (R->A->host.vec - 1) * kKmClasses + km_index(R->k);
+    return solve_class(R->A, R->k);
 }
 
 // A block of at least `bytes` from the pool (or a new one).
@@ -256,7 +256,7 @@ void admit(fs_server *S, std::vector<Request *> &joining)
 
 fs_status step(fs_server *S)
 {
-    constexpr int32_t NC = 2 * kKmClasses;
+    constexpr int32_t NC = kSolveClasses;
     std::vector<Request *> joining;
     admit(S, joining);
     // joiners: state from the pool, b into layout order, x = 0, then their
@@ -286,7 +286,7 @@ fs_status step(fs_server *S)
         joined[cls] = true;
         J.vt = VT_F64;
         J.st = ST_F64;
-        J.vec = 1 + cls / kKmClasses;
+        J.vec = class_vec(cls);
         const hipStream_t st = class_stream(S, cls);
         FS_TRY(batch_build(J, st));
         if (S->o.precond) FS_HIP_TRY(engine_diag_inv(J.L, st));
@@ -313,7 +313,7 @@ fs_status step(fs_server *S)
             B.members = syss;
             B.vt = VT_F64;
             B.st = ST_F64;
-            B.vec = 1 + cls / kKmClasses;
+            B.vec = class_vec(cls);
             FS_TRY(batch_build(B, st));
             S->stable[cls] = 0;
         } else {

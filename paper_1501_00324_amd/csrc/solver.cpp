@@ -218,9 +218,7 @@ fs_status batch_build(Batch &B, hipStream_t s)
         d.gbase = A->d_col16 ? A->d_gbase : nullptr;
         d.st = stage_of(A);
         all_staged &= A->stage_max > 0 || A->n_groups == 0;
-        // (31-bit offsets of the vectors' rows, tiles.h)
-        all_tiles &= A->n_groups == 0 ||
-                     (A->row_tiles && int64_t(S.n) * S.k < (int64_t(1) << 28) - 16);
+        all_tiles &= A->n_groups == 0 || runs_tiles(A, S.k);
         stage = std::max(stage, A->stage_max);
         d.n = S.n;
         d.ngroups = A->n_groups;
@@ -1182,18 +1180,15 @@ extern "C" fs_status cg_solve_batch(int32_t m, const fs_csr_t *A,
             else
                 FS_TRY(load_block(A[i], k[i], X[i], k[i], S.x, s));
         }
-        // one batch per slot vector width and column-count class (both
-        // are template parameters of the kernels)
-        for (int32_t cls = 0; cls < 2 * kKmClasses; ++cls) {
-            const int32_t vec = 1 + cls / kKmClasses, kc = cls % kKmClasses;
+        // one batch per solve_class
+        for (int32_t cls = 0; cls < kSolveClasses; ++cls) {
             Batch Bt;
             Bt.vt = VT_F64;
             Bt.st = ST_F64;
-            Bt.vec = vec;
+            Bt.vec = class_vec(cls);
             std::vector<int32_t> idx;
             for (int32_t i = 0; i < m; ++i)
-                if (A[i]->n_rows > 0 && A[i]->host.vec == vec &&
-                    km_index(k[i]) == kc) {
+                if (A[i]->n_rows > 0 && solve_class(A[i], k[i]) == cls) {
                     Bt.members.push_back(&sys[size_t(i)]);
                     idx.push_back(i);
                 }

@@ -66,3 +66,28 @@ def test_refinement_pace(precision, restart):
         x, d = fs.cg_solve(M, b, use_graph=graph, check_every=12, **opts)
         assert np.array_equal(host(x), host(ref))
         assert (d["iters"], d["outer"]) == (info["iters"], info["outer"])
+
+
+@pytest.mark.parametrize("vec", [1, 2])
+@pytest.mark.parametrize("k", [2, 3, 4, 8, 9])
+def test_batch_of_both_product_forms(k, vec):
+    """Systems whose multi-column products run on the matrix cores (rows that
+    share their columns) beside ones whose do not: every result is that of
+    the system alone."""
+    note("batch of both product forms k=%d vec=%d" % (k, vec))
+    mats = [W.tet_p1(7, physics="elastic", bc="x0"), W.tet_p1(11, bc="all")]
+    mats = [m for m in mats for _ in range(2)]
+    Ms = [make(m, vec=vec) for m in mats]
+    g = np.random.default_rng(10)
+    Bs = [dev(g.uniform(-1, 1, (m.n_rows, k))) for m in mats]
+    alone = [host(fs.cg_solve_multi(M, B)[0]) for M, B in zip(Ms, Bs)]
+    Xs, _ = fs.cg_solve_batch(Ms, Bs)
+    for X, ref in zip(Xs, alone):
+        assert np.array_equal(host(X), ref)
+    srv = fs.Server(check_every=4)
+    subs = [srv.submit(M, B) for M, B in zip(Ms, Bs)]
+    done = srv.drain()
+    srv.close()
+    assert len(done) == len(subs)
+    for (_, X), ref in zip(subs, alone):
+        assert np.array_equal(host(X), ref)
