@@ -246,6 +246,9 @@ fs_status batch_build(Batch &B, hipStream_t s)
         kmax = std::max(kmax, S.k);
     }
     const int32_t nc = int32_t(B.cols.size());
+    // (a larger array may come back at the address of the one it replaces)
+    if (m > B.cap_sys || sb > B.cap_s || vb > B.cap_v || nc > B.cap_c)
+        B.uploaded.clear();
     FS_TRY(ensure_cap(B.d_sys, B.cap_sys, m));
     FS_TRY(ensure_cap(B.d_smap, B.cap_s, sb));
     FS_TRY(ensure_cap(B.d_vmap, B.cap_v, vb));
