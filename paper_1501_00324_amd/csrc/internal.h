@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/fespmv.h"
+#include "pace.h"
 #include "layout.h"
 
 namespace fs {
@@ -260,10 +261,10 @@ struct Batch {
     ColState *d_stage = nullptr, *h_stage = nullptr;
     int32_t cap_sys = 0, cap_s = 0, cap_v = 0, cap_c = 0;
     EngineLaunch L{};
-    // graphs of the two chunk lengths in use (iterations each); they hold
+    // kept graphs and their iterations (pace.h: graph_place); they hold
     // device addresses and grid sizes only, so they last while L does
-    hipGraphExec_t graph[2] = {nullptr, nullptr};
-    int32_t graph_iters[2] = {0, 0};
+    hipGraphExec_t graph[kGraphs] = {};
+    int32_t graph_iters[kGraphs] = {};
     std::vector<int2> cols;           // (member, column) per finalize block
     // pinned staging of stream-ordered descriptor uploads, and the event
     // of the last upload

@@ -157,7 +157,7 @@ fs_status sys_alloc(CgSys &S, fs_csr *A, int32_t k, int32_t vt, int32_t st,
 namespace {
 void drop_graphs(Batch &B)
 {
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < kGraphs; ++i) {
         if (B.graph[i]) (void)hipGraphExecDestroy(B.graph[i]);
         B.graph[i] = nullptr;
         B.graph_iters[i] = 0;
@@ -351,9 +351,8 @@ fs_status batch_iterations(Batch &B, int32_t iters, bool use_graph,
             FS_HIP_TRY(engine_iteration(B.L, s));
         return FS_OK;
     }
-    int slot = B.graph_iters[0] == iters ? 0 : B.graph_iters[1] == iters ? 1 : -1;
-    if (slot < 0) {
-        slot = B.graph[0] && !B.graph[1] ? 1 : 0;
+    const int slot = graph_place(iters);
+    if (B.graph_iters[slot] != iters) {
         if (B.graph[slot]) (void)hipGraphExecDestroy(B.graph[slot]);
         B.graph[slot] = nullptr;
         B.graph_iters[slot] = 0;
@@ -408,53 +407,10 @@ bool any_status(const Batch &B, int32_t st)
     return false;
 }
 
-// The chunks between two looks at the column states.  A solve used to launch
-// check_every iterations at a time, whatever was left to do: a solve of 35
-// iterations launched 64, refinement steps of 9 launched 32 each (an idle
-// iteration of three empty launches takes 5-7 us).  Now the columns' rate
-// of convergence says how many are left; a look never comes later than
-// every check_every iterations, and at each multiple of it, as before.
-// Chunks are multiples of kChunk iterations, replayed as graphs of kChunk
-// and kLongChunk, which the batch keeps.
-constexpr int32_t kChunk = 4, kLongChunk = 16;
-struct Pace {
-    int32_t every = 32;
-    int32_t since = 0;                    // iterations since the start
-    std::vector<double> rr, rate;         // per column: |r|^2 at the last
-    std::vector<int32_t> iter;            //   look, its fall per iteration
-    // iterations of the next chunk, from the states of the last look
-    int32_t next(const Batch &B)
-    {
-        const size_t nc = size_t(B.L.ncols);
-        if (rr.size() != nc) {
-            rr.assign(nc, 0.0);
-            rate.assign(nc, 0.0);
-            iter.assign(nc, 0);
-        }
-        double want = kChunk;
-        for (size_t c = 0; c < nc; ++c) {
-            const ColState &s = B.h_stage[c];
-            if (s.status == CG_RUNNING && s.rr > 0.0 && s.tol2 > 0.0) {
-                const double left = std::log(s.rr / s.tol2);
-                if (s.iter > iter[c] && rr[c] > s.rr && since > 0)
-                    rate[c] = std::log(rr[c] / s.rr) / (s.iter - iter[c]);
-                // unknown rate: two iterations per digit of |r|
-                const double it = rate[c] > 0.0 ? left / rate[c]
-                                                : 0.434 * left;
-                if (it > want) want = it;
-            }
-            rr[c] = s.rr;
-            iter[c] = s.iter;
-        }
-        const int32_t room = every - since % every;
-        int32_t n = room;
-        if (every % kChunk == 0 && want < room)
-            n = std::min(room, (int32_t(std::ceil(want)) + kChunk - 1) /
-                                   kChunk * kChunk);
-        since += n;
-        return n;
-    }
-};
+int32_t next_chunk(Pace &pace, const Batch &B)
+{
+    return pace.next(B.h_stage, size_t(B.L.ncols), CG_RUNNING);
+}
 
 // n iterations for every running column of B, in kept graphs.
 fs_status batch_chunk(Batch &B, int32_t n, bool use_graph, hipStream_t s)
@@ -497,7 +453,7 @@ fs_status run_batch(Batch &B, int32_t check_every, bool use_graph,
     Pace pace;
     pace.every = check_every;
     while (any_status(B, CG_RUNNING)) {
-        FS_TRY(batch_chunk(B, pace.next(B), use_graph, s));
+        FS_TRY(batch_chunk(B, next_chunk(pace, B), use_graph, s));
         FS_TRY(batch_read_states(B, s));
         if (any_status(B, CG_RECURRENCE_MET)) {
             FS_HIP_TRY(engine_residual(B.L, 1, false, s));
@@ -901,7 +857,7 @@ fs_status solve_ir(fs_csr *A, int32_t k, const double *Bc, int64_t ldb,
                     break;
                 }
             }
-            FS_TRY(batch_chunk(BI, pace.next(BI), o.use_graph != 0, s));
+            FS_TRY(batch_chunk(BI, next_chunk(pace, BI), o.use_graph != 0, s));
             FS_TRY(batch_read_states(BI, s));
             if (o.ir_restart && any_status(BI, CG_RECURRENCE_MET)) {
                 // classic refinement confirms the inner solve against its own
@@ -989,9 +945,14 @@ fs_status solve_any(fs_csr *A, int32_t k, const double *B, int64_t ldb,
         return FS_OK;
     }
     DeviceGuard g(A->device);
-    if (o.precision == FS_PREC_F64)
-        return solve_f64(A, k, B, ldb, X, ldx, o, infos, s);
-    return solve_ir(A, k, B, ldb, X, ldx, o, infos, s);
+    const fs_status st =
+        o.precision == FS_PREC_F64
+            ? solve_f64(A, k, B, ldb, X, ldx, o, infos, s)
+            : solve_ir(A, k, B, ldb, X, ldx, o, infos, s);
+    // a solve that failed half-way leaves nothing running on the handle's
+    // workspace and graphs, which the next one may replace
+    if (st != FS_OK && A->stream) (void)hipStreamSynchronize(A->stream);
+    return st;
 }
 
 }  // namespace
@@ -1219,6 +1180,7 @@ extern "C" fs_status cg_solve_batch(int32_t m, const fs_csr_t *A,
                     FS_TRY(store_block(A[i], S.k, S.x, X[i], S.k, s));
                 }
             }
+            if (r != FS_OK) (void)hipStreamSynchronize(s);
             batch_free(Bt);
             FS_TRY(r);
         }
