@@ -49,8 +49,11 @@ struct Pace {
         double want = kChunk;
         for (size_t c = 0; c < nc; ++c) {
             const State &s = states[c];
-            if (s.status == running && s.rr > 0.0 && s.tol2 > 0.0) {
-                const double left = std::log(s.rr / s.tol2);
+            if (s.status == running && s.rr > 0.0) {
+                // a tolerance that underflows (rtol |b| below 1e-162, the
+                // way to ask for maxit iterations) is never met: infinity
+                const double left = s.tol2 > 0.0 ? std::log(s.rr / s.tol2)
+                                                 : HUGE_VAL;
                 if (s.iter > iter[c] && rr[c] > s.rr && since > 0)
                     rate[c] = std::log(rr[c] / s.rr) / (s.iter - iter[c]);
                 // unknown rate: two iterations per digit of |r|

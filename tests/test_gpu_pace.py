@@ -22,3 +22,15 @@ def test_foreign_chunk_lengths_before_the_default():
         x, d = fs.cg_solve(M, b, check_every=every)
         assert np.array_equal(host(x), host(ref)), every
         assert d["iters"] == info["iters"], every
+
+
+def test_all_iterations_of_an_unreachable_tolerance():
+    """A tolerance whose square underflows runs maxit iterations."""
+    note("rtol 1e-200")
+    A = W.config0_poisson2d()
+    b = dev(np.random.default_rng(22).uniform(-1, 1, A.n_rows))
+    M = make(A)
+    ref, _ = fs.cg_solve(M, b, rtol=1e-200, maxit=50, use_graph=0, check_every=1, check=False)
+    x, d = fs.cg_solve(M, b, rtol=1e-200, maxit=50, check=False)
+    assert d["status"] == fs.FS_E_NOT_CONVERGED and d["iters"] == 50
+    assert np.array_equal(host(x), host(ref))

@@ -55,3 +55,19 @@ def test_chunks_follow_the_rate(tmp_path, every):
 """ % every)
     it, looks = map(int, out)
     assert 80 <= it < 84 and looks <= 8
+
+
+def test_tolerance_that_underflows(tmp_path):
+    """rtol |b| whose square is zero is never met: looks every check_every
+    iterations, as for any solve that is far from its end."""
+    out = run_cpp(tmp_path, ["pace.h"], r"""
+    struct State { double rr, tol2; int32_t iter, status; } s{1.0, 0.0, 0, 0};
+    Pace p;
+    for (int i = 0; i < 5; ++i) {
+        const int32_t n = p.next(&s, 1, 0);
+        s.iter += n;
+        s.rr *= 1e-3;
+        std::printf("%d ", n);
+    }
+""")
+    assert out == ["32"] * 5
