@@ -384,6 +384,25 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// f(integral_constant<int, n>) for a uniform n in LO .. HI, each n with a
+// block of its own.  The empty asm tells the blocks apart: the compiler would
+// otherwise merge their equal stores into ones through a chosen pointer, which
+// keeps the arrays f fills in scratch memory.
+template <int LO, int HI, class F>
+__device__ __forceinline__ void with_count(int n, F &&f)
+{
+    if (LO == HI || n == HI) {
+        f(std::integral_constant<int, HI>());
+        asm volatile("" ::"n"(HI));
+    } else if constexpr (LO < HI) {
+        constexpr int M = (LO + HI) / 2;
+        if constexpr (M > LO) {
+            if (n < M) return with_count<LO, M - 1>(n, f);
+        }
+        with_count<M, HI - 1>(n, f);
+    }
+}
+
 // This wavefront's staging buffer in the block's dynamic LDS: `stage` + 1
 // entries per wavefront.
 template <typename ST> __device__ __forceinline__ ST *stage_buffer(int stage)
@@ -409,9 +428,11 @@ __device__ __forceinline__ ST staged_lane_sum(const Group &g, int gi, int lane,
 {
     typedef typename Pack<VT, V>::T PV;
     // slots per batch: 16 halve the loads' latency share for 2-byte values
-    // (config-1 matrix, us: bf16 23.4 with 8, 22.0 with 16; float 32.7 with
-    // 8, 37.1 with 16, whose registers leave 5 wavefronts per SIMD)
-    constexpr int B = sizeof(VT) == 2 ? 16 : 8;
+    // (P1 elasticity 64^3, us: bf16 23.4 with 8, 22.0 with 16; float 32.7
+    // with 8, 37.1 with 16, whose registers leave 5 wavefronts per SIMD).
+    // Single-slot loads (V = 1) are for rows of few slots, mostly under 16
+    // (P1 Laplacian 126^3, bf16: 27.4 with 8, 33.9 with 16).
+    constexpr int B = sizeof(VT) == 2 && V == 2 ? 16 : 8;
     constexpr int U = B / V, L = B / 4;
     const auto gp = gbl(a.grp) + gi;
     const int per = __builtin_amdgcn_readfirstlane(gp->per);
@@ -424,41 +445,40 @@ __device__ __forceinline__ ST staged_lane_sum(const Group &g, int gi, int lane,
     const int width = g.width_lt & 0xffffff;
     const gptr<PV> pv =
         reinterpret_cast<gptr<PV>>(val + long(g.base64) * kWave);
-    const int nb = (width + B - 1) / B, full = width / B;
+    const int nb = (width + B - 1) / B, full = width / B, nch = width / V;
     auto position = [&](int j) {
         const auto p = pl + long(j) * per + me;
         if constexpr (STREAM) return __builtin_nontemporal_load(p);
         else return *p;
     };
+    // R loads of V slots from batch b.  A partial batch has a block of its own
+    // for every length: with a guard per load, each address calculation waits
+    // for the loads before it (P1 Laplacian 126^3, 15 slots per row, f64 / bf16
+    // us: 71.0 / 62.6 so, 61.9 / 27.4 now; 60^3 10.3 / 11.1 and 8.1 / 8.1; gathers
+    // per slot 69.7 / 43.2 and 11.9 / 9.5), and repeating the last load costs
+    // the address unit a useful one (Q1 Laplacian 60^3 in f32 9.7, now 8.9).
+    auto load_some = [&](us4 (&c)[L], PV (&v)[U], int b, auto count) {
+        constexpr int R = decltype(count)::value;
+#pragma unroll
+        for (int l = 0; l < (R * V + 3) / 4; ++l) c[l] = position(b * L + l);
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            v[u] = __builtin_nontemporal_load(pv + (b * U + u) * kWave + lane);
+    };
     auto load = [&](us4 (&c)[L], PV (&v)[U], int b) {
-        if (b < full) {
-#pragma unroll
-            for (int l = 0; l < L; ++l) c[l] = position(b * L + l);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                v[u] = __builtin_nontemporal_load(pv + (b * U + u) * kWave + lane);
-        } else {
-#pragma unroll
-            for (int l = 0; l < L; ++l)
-                if (b * B + 4 * l < width) c[l] = position(b * L + l);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if ((b * U + u) * V < width)
-                    v[u] = __builtin_nontemporal_load(pv + (b * U + u) * kWave +
-                                                      lane);
-        }
+        with_count<1, U>(b < full ? U : nch - b * U, [&](auto count) {
+            load_some(c, v, b, count);
+        });
     };
     ST acc0 = ST(0), acc1 = ST(0);
     auto use = [&](const us4 (&c)[L], const PV (&v)[U], int b) {
-        auto slots = [&](auto all) {
-            ST xv[B];
+        with_count<1, U>(b < full ? U : nch - b * U, [&](auto count) {
+            constexpr int R = decltype(count)::value;
+            ST xv[R * V];
 #pragma unroll
-            for (int i = 0; i < B; ++i)
-                if (decltype(all)::value || b * B + i < width)
-                    xv[i] = xs[c[i / 4][i % 4]];
+            for (int i = 0; i < R * V; ++i) xv[i] = xs[c[i / 4][i % 4]];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (!decltype(all)::value && (b * U + u) * V >= width) continue;
+            for (int u = 0; u < R; ++u) {
                 ST av[V];
                 unpack<VT, ST, V>(v[u], av);
 #pragma unroll
@@ -467,9 +487,7 @@ __device__ __forceinline__ ST staged_lane_sum(const Group &g, int gi, int lane,
                     acc = fma(av[t], xv[u * V + t], acc);
                 }
             }
-        };
-        if (b < full) slots(std::true_type());
-        else slots(std::false_type());
+        });
     };
     us4 c0[L], c1[L];
     PV v0[U], v1[U];
