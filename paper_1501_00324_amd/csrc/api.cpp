@@ -829,6 +829,15 @@ fs_status csr_info(fs_csr_t A, fs_csr_stats *st)
     return FS_OK;
 }
 
+// Forms that the handle's products and value refresh take (internal.h): for
+// the tests, which state the form that each case is meant to run.
+int32_t fs_product_forms(fs_csr_t A)
+{
+    if (!A) return 0;
+    return (A->d_sgrp ? kFormStaged : 0) | (A->row_tiles ? kFormTiles : 0) |
+           (A->refresh_width > 0 ? kFormRefreshTiles : 0);
+}
+
 fs_status csr_get_perm(fs_csr_t A, int32_t *perm_host)
 {
     FS_TRY(check_handle(A));

@@ -118,6 +118,9 @@ constexpr double kTileRows = 2.0;
 // 242 / 237.
 constexpr int64_t kLocCached = int64_t(56) << 20;
 
+// Bits of fs_product_forms (api.cpp).
+constexpr int32_t kFormStaged = 1, kFormTiles = 2, kFormRefreshTiles = 4;
+
 // ------------------------------------------------- batched CG engine state
 // Status of one right-hand side.
 enum { CG_RUNNING = 0, CG_CONVERGED = 1, CG_RECURRENCE_MET = 2,

@@ -39,3 +39,13 @@ def assert_spmv_close(y, y_ref, scale, what=""):
     bad &= ~(both_nan | same_inf)
     assert not bad.any(), "%s: %d rows off, first %s" % (
         what, bad.sum(), np.nonzero(bad)[0][:5])
+
+
+STAGED, TILES, REFRESH_TILES = 1, 2, 4
+
+
+def forms(M):
+    """Forms a handle's products take: STAGED | TILES | REFRESH_TILES."""
+    import paper_1501_00324_amd as fs
+    import ctypes
+    return fs.load().fs_product_forms(ctypes.c_void_p(M._h))

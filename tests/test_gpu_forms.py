@@ -1,0 +1,128 @@
+"""Which form a product takes at the edges of the rules, and the strided forms
+of the multi-column products."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import paper_1501_00324_amd as fs
+from workloads.meshes import CSR
+from tests.gpu_util import STAGED, TILES, REFRESH_TILES, assert_spmv_close, dev, forms, host, make, note
+from tests.test_gpu_stage import CASES, block_matrix
+
+pytestmark = pytest.mark.gpu
+
+# the forms that the cases of tests/test_gpu_stage.py run in.  "single": rows
+# are sorted by length inside windows, so a group references most of its
+# window: 0.46 distinct columns per slot, 0.44 with the slots in pairs, whose
+# padding counts ("single" is staged then; one unknown per node and staged
+# without pairs: tests/test_gpu_stage_widths.py).
+EXPECTED = {"three": STAGED | TILES, "six": STAGED | TILES, "lanes": STAGED | TILES, "empty": STAGED | TILES, "single": 0,
+            "one row": STAGED, "wide": STAGED | TILES, "scattered": 0, "far": STAGED | TILES}
+
+
+@pytest.mark.parametrize("vec", [0, 1, 2])
+@pytest.mark.parametrize("name", sorted(EXPECTED))
+def test_forms_of_the_stage_cases(name, vec):
+    note("forms %s vec=%d" % (name, vec))
+    M = make(block_matrix(seed=7, **CASES[name]), reorder=fs.REORDER_NONE, vec=vec)
+    want = STAGED if name == "single" and vec == 2 else EXPECTED[name]
+    assert forms(M) == want | REFRESH_TILES
+
+
+def long_rows(distinct, rows=64):
+    """One row group of `rows` rows of one node each, that reference
+    `distinct` columns together, every row three quarters of them."""
+    g = np.random.default_rng(distinct)
+    each = distinct * 3 // 4
+    cols = [np.arange(each), np.arange(distinct - each, distinct)]
+    cols += [g.choice(distinct, each, replace=False) for _ in range(rows - 2)]
+    rowptr = np.arange(rows + 1, dtype=np.int32) * each
+    return CSR(rows, 20000, rowptr, np.concatenate(cols).astype(np.int32), g.uniform(-1, 1, rows * each))
+
+
+@pytest.mark.parametrize("distinct,staged", [(1279, True), (1280, True), (1281, False)])
+def test_widest_group(orc, distinct, staged):
+    """A group of 1,280 distinct columns fills the LDS; one more is gathered
+    per slot.  (Lanes fixed to one: all rows in one group.)"""
+    note("widest group %d" % distinct)
+    A = long_rows(distinct)
+    M = make(A, reorder=fs.REORDER_NONE, lanes_min=1, lanes_max=1)
+    assert fs.csr_info(M)["n_groups"] == 1
+    assert bool(forms(M) & STAGED) == staged
+    x = np.random.default_rng(1).uniform(-1, 1, A.n_cols)
+    y = host(fs.spmv(M, dev(x)))
+    assert np.array_equal(y, host(fs.spmv_batch([M], [dev(x)])[0]))
+    assert_spmv_close(y, orc.spmv(A, x), orc.spmv_abs(A, x))
+
+
+@pytest.mark.parametrize("span,staged", [(327680, True), (327681, False)])
+def test_widest_span(orc, span, staged):
+    """Columns of a group spread over 327,680 columns (the bitmap that finds
+    them), and over one more."""
+    note("widest span %d" % span)
+    g = np.random.default_rng(2)
+    shared = np.sort(g.choice(span - 2, 30, replace=False)) + 1
+    cols = np.tile(np.concatenate([[0], shared, [span - 1]]), 64).astype(np.int32)
+    A = CSR(64, span, np.arange(65, dtype=np.int32) * 32, cols, g.uniform(-1, 1, len(cols)))
+    M = make(A, reorder=fs.REORDER_NONE)
+    assert bool(forms(M) & STAGED) == staged
+    x = g.uniform(-1, 1, span)
+    y = host(fs.spmv(M, dev(x)))
+    assert np.array_equal(y, host(fs.spmv_batch([M], [dev(x)])[0]))
+    assert_spmv_close(y, orc.spmv(A, x), orc.spmv_abs(A, x))
+
+
+def strided_spmm(M, X, k, ldx, ldy):
+    """fs spmm on rows of ldx and ldy values; the columns past k of Y keep
+    the sentinel."""
+    import torch
+    Xd = torch.full((M.n_cols, ldx), float("nan"), dtype=torch.float64, device="cuda")
+    Xd[:, :k] = dev(X)
+    Yd = torch.full((M.n_rows, ldy), 7.25, dtype=torch.float64, device="cuda")
+    st = fs.load().spmm(C.c_void_p(M._h), k, C.c_void_p(Xd.data_ptr()), ldx, C.c_void_p(Yd.data_ptr()), ldy, None)
+    assert st == fs.FS_OK, fs.last_error()
+    torch.cuda.synchronize()
+    Y = host(Yd)
+    assert np.all(Y[:, k:] == 7.25)
+    return Y[:, :k]
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 7, 8, 9, 15, 16])
+@pytest.mark.parametrize("name", ["three", "six", "lanes", "single", "wide"])
+def test_rows_longer_than_k(orc, name, k):
+    """Row strides of X and Y over k (odd and even: pairs of columns at
+    8-byte addresses), the caller's numbering and a permuted one; NaN in the
+    unused columns of X reaches nothing."""
+    note("spmm strides %s k=%d" % (name, k))
+    A = block_matrix(seed=23, **CASES[name])
+    X = np.random.default_rng(24).uniform(-1, 1, (A.n_cols, k))
+    ref = orc.spmm(A, X)
+    scale = np.stack([orc.spmv_abs(A, X[:, c]) for c in range(k)], 1)
+    for opts in (dict(reorder=fs.REORDER_NONE, sort_window=1), dict()):
+        M = make(A, **opts)
+        plain = host(fs.spmm(M, dev(X)))
+        for more in (0, 1, 2, 3):
+            Y = strided_spmm(M, X, k, k + more, k + 3 - more)
+            assert np.array_equal(Y, plain)
+            assert_spmv_close(Y, ref, scale, "%s k=%d +%d" % (name, k, more))
+
+
+@pytest.mark.parametrize("ldx", [131007, 131009])
+def test_stride_past_31_bit_offsets(orc, ldx):
+    """The widest rows of X that the matrix-core product's 31-bit byte offsets
+    reach (2,049 columns of 131,007 values are 2^31 - 128 bytes less a few),
+    and rows past them, which take the other form."""
+    import torch
+    note("spmm ldx=%d" % ldx)
+    A = block_matrix(nodes=683, dof=3, per_node=(3, 10), span=20, seed=25)
+    M = make(A, reorder=fs.REORDER_NONE, sort_window=1)
+    assert forms(M) & TILES and A.n_cols == 2049
+    k = 5
+    X = np.random.default_rng(26).uniform(-1, 1, (A.n_cols, k))
+    Xd = torch.zeros(A.n_cols * ldx, dtype=torch.float64, device="cuda").view(A.n_cols, ldx)
+    Xd[:, :k] = dev(X)
+    Y = torch.empty(A.n_rows, k, dtype=torch.float64, device="cuda")
+    assert fs.load().spmm(C.c_void_p(M._h), k, C.c_void_p(Xd.data_ptr()), ldx, C.c_void_p(Y.data_ptr()), k, None) == fs.FS_OK
+    scale = np.stack([orc.spmv_abs(A, X[:, c]) for c in range(k)], 1)
+    assert_spmv_close(host(Y), orc.spmm(A, X), scale)
