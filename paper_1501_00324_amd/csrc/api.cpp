@@ -185,7 +185,11 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
                                   A->d_loc, A->d_scols, s));
     FS_HIP_TRY(hipStreamSynchronize(s));
     A->stage_max = std::max(most, 1);
-    A->row_tiles = double(A->n_rows) >= kTileRows * double(patterns);
+    double lanes = 0.0;
+    for (int i = 0; i < 7; ++i)
+        lanes += double(A->host.groups_by_lanes[i]) * (1 << i);
+    A->tiles = tile_classes(double(A->n_rows), double(patterns),
+                            double(A->slots), lanes / double(ng));
     A->stream_loc = 8 * loc > kLocCached;
     if (A->d_jpos) {
         // the value refresh reads row starts: the inverse map has served,
@@ -834,8 +838,8 @@ fs_status csr_info(fs_csr_t A, fs_csr_stats *st)
 int32_t fs_product_forms(fs_csr_t A)
 {
     if (!A) return 0;
-    return (A->d_sgrp ? kFormStaged : 0) | (A->row_tiles ? kFormTiles : 0) |
-           (A->refresh_width > 0 ? kFormRefreshTiles : 0);
+    return (A->d_sgrp ? kFormStaged : 0) |
+           (A->refresh_width > 0 ? kFormRefreshTiles : 0) | A->tiles << kFormTiles;
 }
 
 fs_status csr_get_perm(fs_csr_t A, int32_t *perm_host)

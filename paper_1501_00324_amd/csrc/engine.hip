@@ -1478,8 +1478,8 @@ hipError_t launch_spmm_f64(const fs_csr *A, int32_t k, const double *X,
 {
     if (A->n_groups == 0) return hipSuccess;
     const dim3 grid((A->n_groups + kWavesPerBlock - 1) / kWavesPerBlock);
-    const int km = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
-    if (A->row_tiles && km >= 4 && tile_fits(A->n_cols, ldx))
+    const int km = km_for(k);
+    if ((A->tiles >> km_index(k) & 1) && tile_fits(A->n_cols, ldx))
         return launch_spmm_tiles(A, k, X, ldx, Y, ldy, yperm, s);
     with_km(km, [&](auto kt) {
         constexpr int KM = decltype(kt)::value;

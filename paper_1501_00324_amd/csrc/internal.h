@@ -9,6 +9,7 @@
 
 #include "../../include/fespmv.h"
 #include "pace.h"
+#include "rules.h"
 #include "layout.h"
 
 namespace fs {
@@ -107,9 +108,6 @@ constexpr double kStageMost = 0.45;
 // Most slots per lane of a group whose rows the value refresh stages (32 KB
 // of LDS per workgroup).
 constexpr int32_t kRefreshWidth = 64;
-// Rows per pattern, over the matrix, from which the multi-column products run
-// on the matrix cores (a pattern is a tile of up to four rows).
-constexpr double kTileRows = 2.0;
 // Positions up to this size are read through the caches, where they stay
 // from one product to the next (256 MB last-level cache); the FP64 product
 // streams larger ones like the values.  Three matrices in turn, us, cached / streamed:
@@ -118,8 +116,9 @@ constexpr double kTileRows = 2.0;
 // 242 / 237.
 constexpr int64_t kLocCached = int64_t(56) << 20;
 
-// Bits of fs_product_forms (api.cpp).
-constexpr int32_t kFormStaged = 1, kFormTiles = 2, kFormRefreshTiles = 4;
+// Bits of fs_product_forms (api.cpp); from bit kFormTiles on the column
+// classes on the matrix cores.
+constexpr int32_t kFormStaged = 1, kFormRefreshTiles = 4, kFormTiles = 8;
 
 // ------------------------------------------------- batched CG engine state
 // Status of one right-hand side.
@@ -160,20 +159,6 @@ struct SysDesc {
     double *hist;                // alpha_j, beta_j per iteration (one
     int32_t hist_cap, pad2;      //   column), or NULL: not recorded
 };
-
-// Column-count class of a system with k right-hand sides: the launch's
-// compile-time column count (1, 2, 4, 8 or 16) and its index 0..4.  Systems
-// share a launch only with systems of the same solve_class, so the
-// arithmetic of a system never depends on the other members of its batch.
-constexpr int kKmClasses = 5;
-inline int32_t km_for(int32_t k)
-{
-    return k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
-}
-inline int32_t km_index(int32_t k)
-{
-    return k <= 1 ? 0 : k <= 2 ? 1 : k <= 4 ? 2 : k <= 8 ? 3 : 4;
-}
 
 // Value / vector type classes of a launch.
 enum { VT_F64 = 0, VT_F32 = 1, VT_BF16 = 2 };
@@ -329,9 +314,9 @@ struct fs_csr {
     uint8_t *d_lpat = nullptr;
     void *d_scols = nullptr;
     int32_t stage_max = 0;
-    // at least kTileRows rows per row pattern: multi-column products run on
-    // the matrix cores
-    bool row_tiles = false;
+    // column classes whose products run on the matrix cores (rules.h:
+    // tile_classes)
+    int32_t tiles = 0;
     int32_t *d_diag = nullptr;     // slot of each layout row's diagonal, -1:
                                    //   none (square matrices)
     bool stream_loc = false;       // positions too large for the caches
@@ -388,13 +373,14 @@ inline StageArgs stage_of(const fs_csr *A)
 // 31-bit offsets of tiles.h.
 inline bool runs_tiles(const fs_csr *A, int32_t k)
 {
-    return (km_for(k) == 4 || km_for(k) == 8) && A->row_tiles &&
+    return (km_for(k) == 4 || km_for(k) == 8) && (A->tiles >> km_index(k) & 1) &&
            int64_t(A->n_rows) * k < (int64_t(1) << 28) - 16;
 }
 
 // Launch class of a solve: its product's form, slots per load and column
-// count.  The tiles add a row's entries in another order than the other
-// form, so a launch holds systems of one of them only.
+// count.  Systems share a launch only with systems of the same class, so the
+// arithmetic of a system never depends on the other members of its batch (the
+// tiles add a row's entries in another order than the other form).
 constexpr int kSolveClasses = 4 * kKmClasses;
 inline int32_t solve_class(const fs_csr *A, int32_t k)
 {
@@ -469,7 +455,7 @@ hipError_t launch_spmv_f64(const fs_csr *A, const double *x, double *y,
 hipError_t launch_spmm_f64(const fs_csr *A, int32_t k, const double *X,
                            int64_t ldx, double *Y, int64_t ldy,
                            const int32_t *yperm, hipStream_t s);
-// The same on the matrix cores (A->row_tiles, k >= 3).
+// The same on the matrix cores (classes of A->tiles).
 hipError_t launch_spmm_tiles(const fs_csr *A, int32_t k, const double *X,
                              int64_t ldx, double *Y, int64_t ldy,
                              const int32_t *yperm, hipStream_t s);

@@ -41,11 +41,14 @@ def assert_spmv_close(y, y_ref, scale, what=""):
         what, bad.sum(), np.nonzero(bad)[0][:5])
 
 
-STAGED, TILES, REFRESH_TILES = 1, 2, 4
+STAGED, REFRESH_TILES = 1, 4
+# products of up to 4, 8 and 16 columns on the matrix cores
+TILES4, TILES8, TILES16 = 1 << 10, 1 << 11, 1 << 12
+TILES = TILES4 | TILES8 | TILES16
 
 
 def forms(M):
-    """Forms a handle's products take: STAGED | TILES | REFRESH_TILES."""
-    import paper_1501_00324_amd as fs
+    """Forms a handle's products take (the bits above)."""
     import ctypes
+    import paper_1501_00324_amd as fs
     return fs.load().fs_product_forms(ctypes.c_void_p(M._h))

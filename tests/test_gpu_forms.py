@@ -7,7 +7,7 @@ import pytest
 
 import paper_1501_00324_amd as fs
 from workloads.meshes import CSR
-from tests.gpu_util import STAGED, TILES, REFRESH_TILES, assert_spmv_close, dev, forms, host, make, note
+from tests.gpu_util import STAGED, TILES, TILES8, TILES16, REFRESH_TILES, assert_spmv_close, dev, forms, host, make, note
 from tests.test_gpu_stage import CASES, block_matrix
 
 pytestmark = pytest.mark.gpu
@@ -17,8 +17,8 @@ pytestmark = pytest.mark.gpu
 # window: 0.46 distinct columns per slot, 0.44 with the slots in pairs, whose
 # padding counts ("single" is staged then; one unknown per node and staged
 # without pairs: tests/test_gpu_stage_widths.py).
-EXPECTED = {"three": STAGED | TILES, "six": STAGED | TILES, "lanes": STAGED | TILES, "empty": STAGED | TILES, "single": 0,
-            "one row": STAGED, "wide": STAGED | TILES, "scattered": 0, "far": STAGED | TILES}
+EXPECTED = {"three": STAGED | TILES, "six": STAGED | TILES, "lanes": STAGED | TILES8 | TILES16, "empty": STAGED | TILES,
+            "single": 0, "one row": STAGED, "wide": STAGED, "scattered": 0, "far": STAGED | TILES}
 
 
 @pytest.mark.parametrize("vec", [0, 1, 2])
@@ -117,7 +117,7 @@ def test_stride_past_31_bit_offsets(orc, ldx):
     note("spmm ldx=%d" % ldx)
     A = block_matrix(nodes=683, dof=3, per_node=(3, 10), span=20, seed=25)
     M = make(A, reorder=fs.REORDER_NONE, sort_window=1)
-    assert forms(M) & TILES and A.n_cols == 2049
+    assert forms(M) & TILES8 and A.n_cols == 2049
     k = 5
     X = np.random.default_rng(26).uniform(-1, 1, (A.n_cols, k))
     Xd = torch.zeros(A.n_cols * ldx, dtype=torch.float64, device="cuda").view(A.n_cols, ldx)
