@@ -117,12 +117,9 @@ fs_status build_refresh_rows(fs_csr *A, const int32_t *h_rp, int64_t &acct,
 }
 
 // The diagonal's slots (square matrices), and the arrays of the staged
-// products (internal.h: StageGroup), kept when every
-// group has at most kStageMax distinct columns and the matrix at most
-// kStageMost of them per slot: a staged group gathers each column once
-// instead of once per slot, and reads its list on top.  After the slot
-// columns (and 16-bit bases) are set, on the same stream, which it
-// synchronises.
+// products (internal.h: StageGroup) where they pay (rules.h: stage_forms).
+// After the slot columns (and 16-bit bases) are set, on the same stream,
+// which it synchronises.
 fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
 {
     const size_t ng = size_t(A->n_groups);
@@ -131,7 +128,8 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
         FS_HIP_TRY(launch_diag_slots(A->d_groups, A->n_groups, A->host.vec,
                                      A->d_col, A->d_diag, s));
     }
-    if (ng == 0 || A->slots == 0) return FS_OK;
+    if (ng == 0 || !stage_pays(double(A->slots), double(kWave) * double(ng)))
+        return FS_OK;
     const bool narrow = A->d_gbase != nullptr;
     int64_t bytes = 0;
     int2 *d_counts = nullptr;
@@ -161,7 +159,9 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
         list += nd;
         patterns += cnt[g].x;
     }
-    if (most > kStageMax || double(list) > kStageMost * double(A->slots)) {
+    const int32_t pays = stage_forms(most, double(list), double(A->slots),
+                                     double(A->n_rows), double(patterns));
+    if (!pays) {
         dfree(A->d_lpat);
         return FS_OK;
     }
@@ -185,6 +185,7 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
                                   A->d_loc, A->d_scols, s));
     FS_HIP_TRY(hipStreamSynchronize(s));
     A->stage_max = std::max(most, 1);
+    A->stage_f64 = pays == 2 ? A->stage_max : 0;
     double lanes = 0.0;
     for (int i = 0; i < 7; ++i)
         lanes += double(A->host.groups_by_lanes[i]) * (1 << i);
@@ -838,7 +839,7 @@ fs_status csr_info(fs_csr_t A, fs_csr_stats *st)
 int32_t fs_product_forms(fs_csr_t A)
 {
     if (!A) return 0;
-    return (A->d_sgrp ? kFormStaged : 0) |
+    return (A->d_sgrp ? kFormStaged : 0) | (A->stage_f64 ? kFormStagedF64 : 0) |
            (A->refresh_width > 0 ? kFormRefreshTiles : 0) | A->tiles << kFormTiles;
 }
 

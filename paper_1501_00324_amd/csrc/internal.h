@@ -101,10 +101,6 @@ struct StageArgs {
     const void *cols;        // column lists: 16-bit offsets from gbase, or
     const int32_t *gbase;    //   (gbase NULL) 32-bit columns
 };
-// Most distinct columns of a group (40 KB of LDS per workgroup), and how
-// many of them per slot, over the matrix, the staging pays for.
-constexpr int32_t kStageMax = 1280;
-constexpr double kStageMost = 0.45;
 // Most slots per lane of a group whose rows the value refresh stages (32 KB
 // of LDS per workgroup).
 constexpr int32_t kRefreshWidth = 64;
@@ -118,7 +114,8 @@ constexpr int64_t kLocCached = int64_t(56) << 20;
 
 // Bits of fs_product_forms (api.cpp); from bit kFormTiles on the column
 // classes on the matrix cores.
-constexpr int32_t kFormStaged = 1, kFormRefreshTiles = 4, kFormTiles = 8;
+constexpr int32_t kFormStaged = 1, kFormStagedF64 = 2, kFormRefreshTiles = 4,
+                  kFormTiles = 8;
 
 // ------------------------------------------------- batched CG engine state
 // Status of one right-hand side.
@@ -308,12 +305,14 @@ struct fs_csr {
     int32_t *d_col = nullptr;
     uint16_t *d_col16 = nullptr;   // 16-bit offsets (index_bits 16), or NULL
     int32_t *d_gbase = nullptr;    // per-group column base for d_col16
-    // staged products (NULL: off) and their widest group
+    // staged products (NULL: off)
     fs::StageGroup *d_sgrp = nullptr;
     uint16_t *d_loc = nullptr;
     uint8_t *d_lpat = nullptr;
     void *d_scols = nullptr;
-    int32_t stage_max = 0;
+    int32_t stage_max = 0;         // distinct columns of the widest group
+    int32_t stage_f64 = 0;         // the same, 0: FP64 gathers per slot
+                                   //   (rules.h: stage_forms)
     // column classes whose products run on the matrix cores (rules.h:
     // tile_classes)
     int32_t tiles = 0;

@@ -168,12 +168,12 @@ void spmv_go(const fs_csr *A, const double *x, double *y,
                         : static_cast<const void *>(A->d_col);
     const size_t lds =
         sizeof(double) * size_t(A->stage_max + 1) * kWavesPerBlock;
-    if (A->d_sgrp && A->stream_loc)
+    if (A->stage_f64 && A->stream_loc)
         hipLaunchKernelGGL((k_spmv_staged<double, double, V, S, N, true>),
                            dim3(spmv_blocks(A->n_groups)), dim3(kBlock), lds,
                            s, A->d_groups, A->n_groups, A->d_val, stage_of(A),
                            A->stage_max, x, y, yperm);
-    else if (A->d_sgrp)
+    else if (A->stage_f64)
         hipLaunchKernelGGL((k_spmv_staged<double, double, V, S, N>),
                            dim3(spmv_blocks(A->n_groups)), dim3(kBlock), lds,
                            s, A->d_groups, A->n_groups, A->d_val, stage_of(A),

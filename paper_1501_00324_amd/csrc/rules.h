@@ -57,4 +57,52 @@ inline int32_t tile_classes(double rows, double patterns, double slots,
            (mean_lanes <= kTileLanes ? wide : 0);
 }
 
+// Which single-column products are staged (internal.h: StageGroup), by
+// distinct columns: 0 none, 1 those on float vectors, 2 FP64 too.  A staged
+// group gathers each of its columns once instead of once per slot, and reads
+// its list on top.  us per product, gathers per slot / staged (rows of one
+// length along a band unless a mesh is named; 6 M to 18 M slots):
+//
+//                                    FP64          FP32          BF16
+// slots per lane
+//   2                                20.0 / 28.4   15.3 / 22.5   12.7 / 27.1
+//   3                                21.9 / 22.1   17.8 / 15.1   15.7 / 16.1
+//     (P1 line, 1 M rows)            11.3 / 11.3    7.8 /  8.7    7.4 /  8.8
+//   4                                15.5 / 18.9   11.7 / 12.0    9.3 / 13.7
+//   5                                21.9 / 17.7   17.3 / 12.1   14.4 / 11.8
+// distinct columns per slot, of 7 slots per row
+//   0.22                             42.9 / 29.4   35.5 / 21.7   32.4 / 19.7
+//   0.52                             43.1 / 30.2   35.6 / 22.4   32.7 / 21.1
+// of 27 (all within 60 columns of the diagonal at 0.23, 230 at 0.48)
+//   0.23                             25.7 / 26.1   20.6 / 16.2   15.7 / 13.8
+//   0.42                             26.0 / 27.7   20.7 / 18.6   16.0 / 16.4
+//   0.55                             26.5 / 28.6   20.9 / 20.0   16.3 / 17.2
+//     (Q1 Laplacian 100^3, 0.34)     52.3 / 48.8   33.5 / 30.9   24.8 / 25.0
+// widest group, rows that share no columns: 32 KB of LDS are five workgroups
+// on a compute unit, 40 KB three or four
+//   680 (45 slots)                   26.8 / 26.2   22.3 / 17.7   17.1 / 13.4
+//   900 (75)                         36.5 / 34.7   27.8 / 22.4   21.6 / 18.7
+//   1080 (45)                        26.4 / 30.5   22.3 / 18.8   17.1 / 14.4
+//   1280 (106)                       49.1 / 52.0   38.4 / 35.6   28.5 / 27.6
+//   1500 (120)                       52.8 / 61.0   42.9 / 39.1   30.6 / 30.5
+// rows that share them in threes: one copy of the positions for three
+//   1280 (153)                       47.5 / 45.6   40.4 / 30.7   30.2 / 21.5
+//   1900 (228, past the LDS limit)   73.5 / 66.2   56.1 / 46.4   41.4 / 32.0
+constexpr int32_t kStageMax = 1280;     // columns of the widest group,
+constexpr int32_t kStageMaxOwn = 1023;  //   FP64 with rows of their own
+constexpr double kStageShared = 1.5;    // rows per pattern from which rows
+                                        //   count as sharing
+constexpr double kStageMost = 0.45;     // columns per slot
+constexpr double kStageSlots = 4.5;     // mean slots per lane
+inline bool stage_pays(double slots, double lanes)
+{
+    return slots >= kStageSlots * lanes;
+}
+inline int32_t stage_forms(int32_t widest, double columns, double slots,
+                           double rows, double patterns)
+{
+    if (widest > kStageMax || columns > kStageMost * slots) return 0;
+    return widest <= kStageMaxOwn || rows >= kStageShared * patterns ? 2 : 1;
+}
+
 }  // namespace fs

@@ -10,7 +10,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 def run_cpp(tmp_path, headers, body):
     """Words printed by `body` (the statements of main)."""
     src = tmp_path / "harness.cpp"
-    src.write_text("#include <cstdio>\n%s\nusing namespace fs;\nint main()\n{\n%s\n}\n" % (
+    src.write_text("#include <cstdio>\n#include <initializer_list>\n%s\nusing namespace fs;\nint main()\n{\n%s\n}\n" % (
         "\n".join('#include "%s"' % h for h in headers), body))
     exe = tmp_path / "harness"
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)

@@ -7,7 +7,7 @@ import pytest
 
 import paper_1501_00324_amd as fs
 from workloads.meshes import CSR
-from tests.gpu_util import STAGED, TILES, TILES8, TILES16, REFRESH_TILES, assert_spmv_close, dev, forms, host, make, note
+from tests.gpu_util import STAGED, STAGED64, TILES, TILES8, TILES16, REFRESH_TILES, assert_spmv_close, dev, forms, host, make, note
 from tests.test_gpu_stage import CASES, block_matrix
 
 pytestmark = pytest.mark.gpu
@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 # padding counts ("single" is staged then; one unknown per node and staged
 # without pairs: tests/test_gpu_stage_widths.py).
 EXPECTED = {"three": STAGED | TILES, "six": STAGED | TILES, "lanes": STAGED | TILES8 | TILES16, "empty": STAGED | TILES,
-            "single": 0, "one row": STAGED, "wide": STAGED, "scattered": 0, "far": STAGED | TILES}
+            "single": 0, "one row": 0, "wide": STAGED, "scattered": 0, "far": STAGED | TILES}
 
 
 @pytest.mark.parametrize("vec", [0, 1, 2])
@@ -27,29 +27,42 @@ def test_forms_of_the_stage_cases(name, vec):
     note("forms %s vec=%d" % (name, vec))
     M = make(block_matrix(seed=7, **CASES[name]), reorder=fs.REORDER_NONE, vec=vec)
     want = STAGED if name == "single" and vec == 2 else EXPECTED[name]
-    assert forms(M) == want | REFRESH_TILES
+    assert forms(M) == want | (STAGED64 if want else 0) | REFRESH_TILES
 
 
-def long_rows(distinct, rows=64):
-    """One row group of `rows` rows of one node each, that reference
-    `distinct` columns together, every row three quarters of them."""
+def test_one_row(orc):
+    note("one staged row")
+    A = CSR(1, 9, np.array([0, 7], np.int32), np.array([8, 0, 3, 5, 4, 2, 7], np.int32), np.arange(1.0, 8.0))
+    M = make(A)
+    assert forms(M) & STAGED64
+    x = np.arange(9.0)
+    assert np.array_equal(host(fs.spmv(M, dev(x))), orc.spmv(A, x))
+
+
+def long_rows(distinct, shared, rows=64):
+    """One row group of `rows` rows that reference `distinct` columns
+    together, every row three quarters of them, `shared` rows the same."""
     g = np.random.default_rng(distinct)
     each = distinct * 3 // 4
     cols = [np.arange(each), np.arange(distinct - each, distinct)]
-    cols += [g.choice(distinct, each, replace=False) for _ in range(rows - 2)]
+    cols += [g.choice(distinct, each, replace=False) for _ in range(rows)]
+    cols = [c for c in cols for _ in range(shared)][:rows]
     rowptr = np.arange(rows + 1, dtype=np.int32) * each
     return CSR(rows, 20000, rowptr, np.concatenate(cols).astype(np.int32), g.uniform(-1, 1, rows * each))
 
 
-@pytest.mark.parametrize("distinct,staged", [(1279, True), (1280, True), (1281, False)])
-def test_widest_group(orc, distinct, staged):
+@pytest.mark.parametrize("shared", [1, 3])
+@pytest.mark.parametrize("distinct", [1023, 1024, 1280, 1281])
+def test_widest_group(orc, distinct, shared):
     """A group of 1,280 distinct columns fills the LDS; one more is gathered
-    per slot.  (Lanes fixed to one: all rows in one group.)"""
-    note("widest group %d" % distinct)
-    A = long_rows(distinct)
+    per slot, in FP64 over 1,023 where the rows do not share their columns.
+    (Lanes fixed to one: all rows in one group.)"""
+    note("widest group %d shared=%d" % (distinct, shared))
+    A = long_rows(distinct, shared)
     M = make(A, reorder=fs.REORDER_NONE, lanes_min=1, lanes_max=1)
     assert fs.csr_info(M)["n_groups"] == 1
-    assert bool(forms(M) & STAGED) == staged
+    assert bool(forms(M) & STAGED) == (distinct <= 1280)
+    assert bool(forms(M) & STAGED64) == (distinct <= (1280 if shared == 3 else 1023))
     x = np.random.default_rng(1).uniform(-1, 1, A.n_cols)
     y = host(fs.spmv(M, dev(x)))
     assert np.array_equal(y, host(fs.spmv_batch([M], [dev(x)])[0]))

@@ -1,4 +1,4 @@
-"""The rule that sends multi-column products to the matrix cores (host)."""
+"""The rules that choose the products' forms (host)."""
 import pytest
 
 from tests.host_harness import run_cpp
@@ -24,3 +24,26 @@ def test_tile_classes(tmp_path, what, rows, patterns, slots, lanes, classes):
     out = run_cpp(tmp_path, ["rules.h"], 'std::printf("%%d\\n", tile_classes(%s, %s, %s, %s));' % (
         float(rows), float(patterns), float(slots), float(lanes)))
     assert out == [str(classes)], what
+
+
+@pytest.mark.parametrize("what,widest,columns,slots,rows,patterns,forms", [
+    ("P1 elasticity", 400, 9e5, 9e6, 2e5, 7e4, 2),
+    ("P1 Laplacian", 300, 4e5, 1e6, 7e4, 7e4, 2),
+    ("45 % of the slots", 300, 4.5e5, 1e6, 7e4, 7e4, 2),
+    ("over it", 300, 4.6e5, 1e6, 7e4, 7e4, 0),
+    ("rows of their own, 32 KB of LDS", 1023, 1e5, 1e6, 2e4, 2e4, 2),
+    ("over it", 1024, 1e5, 1e6, 2e4, 2e4, 1),
+    ("shared rows", 1280, 1e5, 1e6, 2e4, 1e4, 2),
+    ("over the limit", 1281, 1e5, 1e6, 2e4, 1e4, 0),
+])
+def test_stage_forms(tmp_path, what, widest, columns, slots, rows, patterns, forms):
+    out = run_cpp(tmp_path, ["rules.h"], 'std::printf("%%d\\n", stage_forms(%d, %s, %s, %s, %s));' % (
+        widest, float(columns), float(slots), float(rows), float(patterns)))
+    assert out == [str(forms)], what
+
+
+def test_rows_too_short_to_stage(tmp_path):
+    out = run_cpp(tmp_path, ["rules.h"], r"""
+    for (int w : {1, 3, 4, 5, 7}) std::printf("%d ", int(stage_pays(64.0 * w, 64.0)));
+""")
+    assert out == ["0", "0", "0", "1", "1"]
