@@ -427,12 +427,10 @@ __device__ __forceinline__ ST staged_lane_sum(const Group &g, int gi, int lane,
                                               ST *xs)
 {
     typedef typename Pack<VT, V>::T PV;
-    // slots per batch: 16 halve the loads' latency share for 2-byte values
-    // (P1 elasticity 64^3, us: bf16 23.4 with 8, 22.0 with 16; float 32.7
-    // with 8, 37.1 with 16, whose registers leave 5 wavefronts per SIMD).
-    // Single-slot loads (V = 1) are for rows of few slots, mostly under 16
-    // (P1 Laplacian 126^3, bf16: 27.4 with 8, 33.9 with 16).
-    constexpr int B = sizeof(VT) == 2 && V == 2 ? 16 : 8;
+    // slots per batch; 16 need registers that cost wavefronts (us, 8 / 16:
+    // P1 elasticity 64^3 f32 32.7 / 37.1, bf16 20.7 / 21.5; bf16 Q1 Laplacian
+    // 126^3 45.3 / 47.3, 2-D P1 elasticity 700^2 12.3 / 13.0)
+    constexpr int B = 8;
     constexpr int U = B / V, L = B / 4;
     const auto gp = gbl(a.grp) + gi;
     const int per = __builtin_amdgcn_readfirstlane(gp->per);

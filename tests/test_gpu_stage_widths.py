@@ -1,6 +1,5 @@
 """Staged products over every row length: the last batch of a row's slots has
-a block of its own for each of its lengths (batches of 8, of 16 for BF16 in
-pairs)."""
+a block of its own for each of its lengths (batches of 8)."""
 import numpy as np
 import pytest
 
