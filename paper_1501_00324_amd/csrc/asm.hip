@@ -118,10 +118,21 @@ __global__ __launch_bounds__(kBlock) void k_interleave_offsets(
 // for.  12 (11 without the vector) load instructions per eight steps instead
 // of 32 (24).  Elements of four to seven unknowns, whose batches hold up to
 // 16 rows, take two loads (EL) of element rows per eight steps; smaller ones
-// load every step's lane by lane (EL = 0), four steps at a time.  Steps past a batch's last one are skipped, lanes without work
-// add 0.0 into a private dummy slot past the group region.  With ORD the
-// element rows come from a buffer stored in the plan's own order (row
-// rec * rows + q), so they are read contiguously and ea is not needed.
+// load every step's lane by lane (EL = 0), four steps at a time.  Lanes without
+// work add 0.0 into a private dummy slot past the group region.
+//
+// With ORD the element rows come from a buffer stored in the plan's own order
+// (row rec * rows + q), so they are read contiguously and ea is not needed: a
+// step's values and offsets are requested together, and looking offsets up
+// ahead only puts their wait before the values' (elasticity on 20^3 nodes
+// 23.0 us with, 17.5 without).
+//
+// LAT: few row groups, whose time is the chain of one wavefront.  The next
+// indices are then requested without a branch, which would make them wait for
+// the values before them (asm_system of elasticity on 12^3 nodes, 81 groups,
+// 18.8 -> 16.0 us; on 20^3, 375 groups, 26.4 -> 23.1); with more groups the
+// branch costs less than the extra requests (64^3 493 / 501 us, triangles
+// 400^2, 2,500 groups, 12.9 / 13.9).
 //
 // BIG: element matrices larger together than the last-level cache.  An
 // element is read by the groups of all its nodes, about a level of the
@@ -131,7 +142,7 @@ __global__ __launch_bounds__(kBlock) void k_interleave_offsets(
 // groups side by side, and the values stream out past the caches.  Smaller
 // data keeps the contiguous ranges (P1 Laplacian 70^3, 252 MB: 203 us, 218
 // in chunks).
-template <int U, bool WR, bool ORD, int EL, bool BIG>
+template <int U, bool WR, bool ORD, int EL, bool BIG, bool LAT>
 __global__ __launch_bounds__(kBlock) void k_assemble_lds(
     const int4 *__restrict__ gdesc, const int4 *__restrict__ bdesc,
     const int *__restrict__ ea, const us4 *__restrict__ off, int nde,
@@ -180,16 +191,19 @@ __global__ __launch_bounds__(kBlock) void k_assemble_lds(
         const auto p = po + (long(d.z) + (k >> 2)) * kWave + lane;
         x.o[0] = __builtin_nontemporal_load(p);
         if constexpr (U == 8) {
-            if (k + 4 < d.y) x.o[1] = __builtin_nontemporal_load(p + kWave);
+            if constexpr (LAT)
+                x.o[1] = __builtin_nontemporal_load(p + (k + 4 < d.y ? kWave : 0));
+            else if (k + 4 < d.y)
+                x.o[1] = __builtin_nontemporal_load(p + kWave);
         }
-        if constexpr (!ORD && EA1) {
+        if constexpr (EA1) {
             // lane u * rows + q: step u of row q (past the batch: its last)
 #pragma unroll
             for (int l = 0; l < EL; ++l) {
                 const int i = min((k + l * UL) * rows + lane, d.y * rows - 1);
                 x.e[l] = __builtin_nontemporal_load(pe + long(d.x) * rows + i);
             }
-        } else if constexpr (!ORD) {
+        } else {
 #pragma unroll
             for (int u = 0; u < U; ++u)
                 if (k + u < d.y)
@@ -198,86 +212,122 @@ __global__ __launch_bounds__(kBlock) void k_assemble_lds(
         }
     };
     int j = wave;
-    int4 d = batch(j), dn = batch(j + kWavesPerBlock);
-    Index nx;
-    if (j < gd.w && d.y > 0) load(nx, d, 0);
-    for (; j < gd.w; j += kWavesPerBlock) {
-        double racc = 0.0;
-        for (int k = 0; k < d.y; k += U) {
-            const Index x = nx;
-            int o[U], e[U];
-            double v[U], w[EA1 ? EL : 1];
+    if constexpr (ORD) {
+        // a step's values are `rows` rows of nde, wherever its offsets lie:
+        // both are requested together, nothing is left to look up ahead
+        const int len = rows * nde, at = qc * nde + b;
+        for (; j < gd.w; j += kWavesPerBlock) {
+            const int4 d = batch(j);
+            const auto p = pk + long(d.x) * len + at;
+            const auto po4 = po + long(d.z) * kWave + lane;
+            for (int k = 0; k < d.y; k += U) {
+                us4 o[2];
+                double v[U];
+                with_count<1, U>(min(U, d.y - k), [&](auto count) {
+                    constexpr int R = decltype(count)::value;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                o[u] = x.o[u >> 2][u & 3];
-                if (u >= 4 && k + 4 >= d.y) o[u] = 0xffff;
-                if constexpr (ORD) e[u] = 0;
-                else if constexpr (EA1) e[u] = __shfl(x.e[u / UL], (u % UL) * rows + qc, kWave);
-                else e[u] = k + u < d.y ? x.e[u] : -1;
+                    for (int c = 0; 4 * c < R; ++c)
+                        o[c] = __builtin_nontemporal_load(po4 + (k / 4 + c) * kWave);
+#pragma unroll
+                    for (int u = 0; u < R; ++u)
+                        v[u] = __builtin_nontemporal_load(p + long(k + u) * len);
+#pragma unroll
+                    for (int u = 0; u < R; ++u) {
+                        // (rows of dropped element rows carry 0xffff only)
+                        const int to = o[u / 4][u % 4];
+                        const bool use = act && to != 0xffff;
+                        acc[use ? to : dummy] += use ? v[u] : 0.0;
+                    }
+                });
             }
-            if constexpr (WR && EA1) {
+        }
+    } else {
+        int4 d = batch(j), dn = batch(j + kWavesPerBlock);
+        Index nx;
+        if (j < gd.w && d.y > 0) load(nx, d, 0);
+        for (; j < gd.w; j += kWavesPerBlock) {
+            double racc = 0.0;
+            for (int k = 0; k < d.y; k += U) {
+                const Index x = nx;
+                int o[U], e[U];
+                double v[U], w[EA1 ? EL : 1];
 #pragma unroll
-                for (int l = 0; l < EL; ++l) {
-                    const bool ok = lane < UL * rows && x.e[l] >= 0;
-                    w[l] = gbl(re)[ok ? x.e[l] : 0];
-                    w[l] = ok ? w[l] : 0.0;
+                for (int u = 0; u < U; ++u) {
+                    o[u] = x.o[u >> 2][u & 3];
+                    if (u >= 4 && k + 4 >= d.y) o[u] = 0xffff;
+                    if constexpr (EA1) e[u] = __shfl(x.e[u / UL], (u % UL) * rows + qc, kWave);
+                    else e[u] = k + u < d.y ? x.e[u] : -1;
                 }
-            }
-            bool use[U];
-            auto value = [&](int u) {
-                use[u] = act && o[u] != 0xffff && (ORD || e[u] >= 0);
-                // (rows of dropped element rows carry offsets 0xffff only)
-                if constexpr (ORD)
-                    v[u] = __builtin_nontemporal_load(
-                        pk + ((long(d.x) + k + u) * rows + qc) * nde + b);
-                else
+                if constexpr (WR && EA1) {
+#pragma unroll
+                    for (int l = 0; l < EL; ++l) {
+                        const bool ok = lane < UL * rows && x.e[l] >= 0;
+                        w[l] = gbl(re)[ok ? x.e[l] : 0];
+                        w[l] = ok ? w[l] : 0.0;
+                    }
+                }
+                bool use[U];
+                auto value = [&](int u) {
+                    use[u] = act && o[u] != 0xffff && e[u] >= 0;
                     v[u] = pk[long(use[u] ? e[u] : 0) * nde + b];
-            };
-            // all loads before the first use: a whole block has no branches
-            if (k + U <= d.y) {
+                };
+                // all loads before the first use, in halves: a guard per load would
+                // make each wait for the one before.  Steps past the batch's last
+                // have no lanes in use and read the first value.
 #pragma unroll
-                for (int u = 0; u < U; ++u) value(u);
-            } else {
+                for (int u = 0; u < U / 2; ++u) value(u);
+                if (k + U / 2 < d.y) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    use[u] = false;
-                    v[u] = 0.0;
-                    if (k + u < d.y) value(u);
+                    for (int u = U / 2; u < U; ++u) value(u);
+                } else {
+#pragma unroll
+                    for (int u = U / 2; u < U; ++u) {
+                        use[u] = false;
+                        v[u] = 0.0;
+                    }
                 }
-            }
-            double wu[U];
-            if constexpr (WR && !EA1) {
+                double wu[U];
+                if constexpr (WR && !EA1) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const bool ok = act && b == 0 && e[u] >= 0;
-                    wu[u] = ok ? gbl(re)[ok ? e[u] : 0] : 0.0;
+                    for (int u = 0; u < U; ++u) {
+                        const bool ok = act && b == 0 && e[u] >= 0;
+                        wu[u] = ok ? gbl(re)[ok ? e[u] : 0] : 0.0;
+                    }
                 }
-            }
-            // the next indices, behind the values in flight
-            if (k + U < d.y) load(nx, d, k + U);
-            else if (j + kWavesPerBlock < gd.w && dn.y > 0) load(nx, dn, 0);
-            if constexpr (WR && EA1) {
+                // the next indices, behind the values in flight
+                if constexpr (LAT) {
+                    // of this batch, or the next one's first (a batch without any:
+                    // this one's once more)
+                    const bool more = k + U < d.y, go = !more && dn.y > 0;
+                    load(nx, go ? dn : d, more ? k + U : 0);
+                } else if (k + U < d.y) {
+                    load(nx, d, k + U);
+                } else if (j + kWavesPerBlock < gd.w && dn.y > 0) {
+                    load(nx, dn, 0);
+                }
+                if constexpr (WR && EA1) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        wu[u] = __shfl(w[u / UL], (u % UL) * rows + qc, kWave);
+                }
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    wu[u] = __shfl(w[u / UL], (u % UL) * rows + qc, kWave);
-            }
+                    acc[use[u] ? o[u] : dummy] += use[u] ? v[u] : 0.0;
+                if constexpr (WR) {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                acc[use[u] ? o[u] : dummy] += use[u] ? v[u] : 0.0;
+                    for (int u = 0; u < U; ++u)
+                        if (k + u < d.y) racc += wu[u];
+                }
+            }
             if constexpr (WR) {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (k + u < d.y) racc += wu[u];
+                const int rr = j * rows + q;
+                const Group lg = load_group(gbl(groups), g);
+                if (act && b == 0 && rr < lg.nrows) r[perm[lg.row0 + rr]] = racc;
             }
+            if (d.y == 0 && j + kWavesPerBlock < gd.w && dn.y > 0) load(nx, dn, 0);
+            d = dn;
+            dn = batch(j + 2 * kWavesPerBlock);
         }
-        if constexpr (WR) {
-            const int rr = j * rows + q;
-            const Group lg = load_group(gbl(groups), g);
-            if (act && b == 0 && rr < lg.nrows) r[perm[lg.row0 + rr]] = racc;
-        }
-        if (d.y == 0 && j + kWavesPerBlock < gd.w && dn.y > 0) load(nx, dn, 0);
-        d = dn;
-        dn = batch(j + 2 * kWavesPerBlock);
     }
     __syncthreads();
     const long base = long(gd.x) * kWave;
@@ -295,6 +345,10 @@ __global__ __launch_bounds__(kBlock) void k_assemble_lds(
 
 }  // namespace
 
+// Row groups up to which the launch is one wavefront's chain (two workgroups
+// on a compute unit; both sides' times at the kernel).
+constexpr int32_t kAsmFew = 512;
+
 hipError_t launch_assemble_lds(const AsmLdsPlan &P, const double *ke,
                                double *val, float *f32, uint16_t *bf16,
                                const Group *groups, const int32_t *perm,
@@ -304,12 +358,13 @@ hipError_t launch_assemble_lds(const AsmLdsPlan &P, const double *ke,
     if (P.ngroups == 0) return hipSuccess;
     const size_t lds = sizeof(double) * (size_t(P.region_max) +
                                          size_t(P.region_max / kWave) + kWave);
-    auto go = [&](auto u, auto wr, auto ord, auto el, auto big) {
+    auto go = [&](auto u, auto wr, auto ord, auto el, auto big, auto lat) {
         hipLaunchKernelGGL((k_assemble_lds<decltype(u)::value,
                                            decltype(wr)::value,
                                            decltype(ord)::value,
                                            decltype(el)::value,
-                                           decltype(big)::value>),
+                                           decltype(big)::value,
+                                           decltype(lat)::value>),
                            dim3(P.ngroups), dim3(kBlock), lds, s,
                            reinterpret_cast<const int4 *>(P.d_gdesc),
                            reinterpret_cast<const int4 *>(P.d_bdesc), P.d_ea,
@@ -324,15 +379,16 @@ hipError_t launch_assemble_lds(const AsmLdsPlan &P, const double *ke,
     const std::integral_constant<int, 1> one;
     const std::integral_constant<int, 2> two;
     auto sized = [&](auto u, auto wr, auto el) {
-        if (P.big) go(u, wr, no, el, yes);
-        else go(u, wr, no, el, no);
+        if (P.big) go(u, wr, no, el, yes, no);
+        else if (P.ngroups <= kAsmFew) go(u, wr, no, el, no, yes);
+        else go(u, wr, no, el, no, no);
     };
     auto stepped = [&](auto wr) {
         if (8 * P.rows <= kWave) sized(eight, wr, one);
         else if (4 * P.rows <= kWave) sized(eight, wr, two);
         else sized(four, wr, none);
     };
-    if (ordered) go(eight, no, yes, none, no);
+    if (ordered) go(eight, no, yes, none, no, no);
     else if (re) stepped(yes);
     else stepped(no);
     return hipGetLastError();
