@@ -1396,8 +1396,12 @@ hipError_t permute_rows(int32_t n, int32_t k, const int32_t *perm,
                        reinterpret_cast<uintptr_t>(dst) % 16 == 0;
     auto go = [&](auto to, auto w) {
         constexpr int W = decltype(w)::value;
+        // two pairs a thread from 4,096 workgroups on: launching one each for
+        // 27 MB of P1 Laplacian columns takes 13.9 us (single values 12.5)
+        const long items = total / W, per = W == 2 && items > 4096 * kBlock ? 2 : 1;
         hipLaunchKernelGGL((k_permute_rows<decltype(to)::value, W>),
-                           dim3(flat_blocks(total / W)), dim3(kBlock), 0, s,
+                           dim3(flat_blocks((items + per - 1) / per)),
+                           dim3(kBlock), 0, s,
                            long(n), unsigned(k / W), perm, src, long(lds), dst,
                            long(ldd));
     };
