@@ -92,16 +92,12 @@ namespace {
 // Row starts and byte-wide in-row positions of the slots (the value
 // refresh reads one byte per slot instead of the 4-byte inverse map), for
 // matrices whose rows hold at most 255 entries and whose positions fit 32
-// bits; otherwise the refresh keeps the inverse map.  After the inverse map
-// is built, on the same stream.
-fs_status build_refresh_rows(fs_csr *A, const int32_t *h_rp, int64_t &acct,
-                             hipStream_t s)
+// bits; otherwise the refresh keeps the inverse map.
+fs_status alloc_refresh(fs_csr *A, int32_t maxlen, int64_t &acct)
 {
-    if (A->slots == 0 || A->nnz > INT32_MAX) return FS_OK;
-    int32_t maxlen = 0;
-    for (int32_t i = 0; i < A->n_rows; ++i)
-        maxlen = std::max(maxlen, h_rp[size_t(i) + 1] - h_rp[size_t(i)]);
-    if (maxlen > 255) return FS_OK;
+    if (A->slots > 0 && (A->nnz > INT32_MAX || maxlen > 255))
+        return dalloc(&A->d_imap, A->slots, acct);
+    if (A->slots == 0) return FS_OK;
     FS_TRY(dalloc(&A->d_jpos, A->slots, acct));
     FS_TRY(dalloc(&A->d_rstart, A->n_rows, acct));
     for (const Group &g : A->host.groups) {
@@ -111,42 +107,41 @@ fs_status build_refresh_rows(fs_csr *A, const int32_t *h_rp, int64_t &acct,
             break;
         }
     }
-    FS_HIP_TRY(launch_refresh_rows(A->d_groups, A->n_groups, A->host.vec,
-                                   A->d_imap, A->d_jpos, A->d_rstart, s));
     return FS_OK;
 }
 
-// The diagonal's slots (square matrices), and the arrays of the staged
-// products (internal.h: StageGroup) where they pay (rules.h: stage_forms).
-// After the slot columns (and 16-bit bases) are set, on the same stream,
-// which it synchronises.
-fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
+// A device array that the build can do without: false (and no error) when
+// there is no memory for it.
+template <class T>
+fs_status dalloc_spare(T **p, int64_t n, int64_t &acct, bool &have)
 {
-    const size_t ng = size_t(A->n_groups);
-    if (A->n_rows == A->n_cols && ng > 0) {
-        FS_TRY(dalloc(&A->d_diag, A->n_rows, acct));
-        FS_HIP_TRY(launch_diag_slots(A->d_groups, A->n_groups, A->host.vec,
-                                     A->d_col, A->d_diag, s));
-    }
-    if (ng == 0 || !stage_pays(double(A->slots), double(kWave) * double(ng)))
-        return FS_OK;
-    const bool narrow = A->d_gbase != nullptr;
-    int64_t bytes = 0;
-    int2 *d_counts = nullptr;
-    FS_TRY(dalloc(&d_counts, A->n_groups, bytes));
-    struct Scratch {
-        int2 *&p;
-        ~Scratch() { dfree(p); }
-    } scratch{d_counts};
-    bytes = 0;
-    FS_TRY(dalloc(&A->d_lpat, int64_t(ng) * kWave, bytes));
+    const fs_status st = dalloc(p, n, acct);
+    have = st == FS_OK;
+    if (st != FS_E_OOM) return st;
+    clear_error();
+    return FS_OK;
+}
+
+// First half of the staged products' build (internal.h: StageGroup): row
+// patterns and distinct columns of every group to counts (device, one entry
+// per group), asynchronously.  `narrow`: columns of a group that span 65,536
+// or more need not be counted (distinct columns -1).
+fs_status count_stage(fs_csr *A, bool narrow, int2 *counts, hipStream_t s)
+{
     FS_HIP_TRY(launch_stage_count(A->d_groups, A->n_groups, A->host.vec,
-                                  A->d_col, narrow, A->d_lpat, d_counts, s));
-    std::vector<int2> cnt(ng);
-    FS_HIP_TRY(hipMemcpyAsync(cnt.data(), d_counts, sizeof(int2) * ng,
-                              hipMemcpyDeviceToHost, s));
-    FS_HIP_TRY(hipStreamSynchronize(s));
-    std::vector<StageGroup> grp(ng);
+                                  A->d_col, narrow, A->d_lpat, counts, s));
+    return FS_OK;
+}
+
+// Second half, where they pay (rules.h: stage_forms) and there is memory for
+// them; else A->d_lpat is given back.  grp is read by copies on stream s.
+fs_status build_stage(fs_csr *A, const std::vector<int2> &cnt,
+                      std::vector<StageGroup> &grp, int64_t &acct,
+                      hipStream_t s)
+{
+    const size_t ng = cnt.size();
+    const bool narrow = A->d_gbase != nullptr;
+    grp.resize(ng);
     int64_t loc = 0, list = 0, patterns = 0;
     int32_t most = 0;
     for (size_t g = 0; g < ng; ++g) {
@@ -161,29 +156,24 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
     }
     const int32_t pays = stage_forms(most, double(list), double(A->slots),
                                      double(A->n_rows), double(patterns));
-    if (!pays) {
-        dfree(A->d_lpat);
-        return FS_OK;
-    }
+    int64_t bytes = int64_t(ng) * kWave;      // d_lpat
+    bool have = pays > 0;
     char *cols = nullptr;
-    fs_status st = dalloc(&A->d_loc, 4 * loc, bytes);
-    if (st == FS_OK) st = dalloc(&cols, list * (narrow ? 2 : 4), bytes);
+    if (have) FS_TRY(dalloc_spare(&A->d_loc, 4 * loc, bytes, have));
+    if (have) FS_TRY(dalloc_spare(&cols, list * (narrow ? 2 : 4), bytes, have));
     A->d_scols = cols;
-    if (st == FS_OK) st = dalloc(&A->d_sgrp, A->n_groups, bytes);
-    if (st != FS_OK) {
-        // no room: the unstaged products need none of it
+    if (have) FS_TRY(dalloc_spare(&A->d_sgrp, A->n_groups, bytes, have));
+    if (!have) {
         dfree(A->d_lpat);
         dfree(A->d_loc);
         dfree(A->d_scols);
-        if (st == FS_E_OOM) clear_error();
-        return st == FS_E_OOM ? FS_OK : st;
+        return FS_OK;
     }
     FS_HIP_TRY(hipMemcpyAsync(A->d_sgrp, grp.data(), sizeof(StageGroup) * ng,
                               hipMemcpyHostToDevice, s));
     FS_HIP_TRY(launch_stage_lists(A->d_groups, A->n_groups, A->host.vec,
                                   A->d_col, A->d_gbase, A->d_sgrp, A->d_lpat,
                                   A->d_loc, A->d_scols, s));
-    FS_HIP_TRY(hipStreamSynchronize(s));
     A->stage_max = std::max(most, 1);
     A->stage_f64 = pays == 2 ? A->stage_max : 0;
     double lanes = 0.0;
@@ -192,14 +182,21 @@ fs_status build_stage(fs_csr *A, int64_t &acct, hipStream_t s)
     A->tiles = tile_classes(double(A->n_rows), double(patterns),
                             double(A->slots), lanes / double(ng));
     A->stream_loc = 8 * loc > kLocCached;
-    if (A->d_jpos) {
-        // the value refresh reads row starts: the inverse map has served,
-        // and is larger than what was added here
-        dfree(A->d_imap);
-        bytes -= A->slots * int64_t(sizeof(int32_t));
-    }
     acct += bytes;
     return FS_OK;
+}
+
+bool stage_wanted(const fs_csr *A)
+{
+    return A->n_groups > 0 &&
+           stage_pays(double(A->slots), double(kWave) * double(A->n_groups));
+}
+
+int32_t longest_row(int32_t n_rows, const int32_t *rp)
+{
+    int32_t m = 0;
+    for (int32_t i = 0; i < n_rows; ++i) m = std::max(m, rp[i + 1] - rp[i]);
+    return m;
 }
 
 // Device handle from host structure arrays (layout built here) and device
@@ -226,6 +223,7 @@ fs_status create_from_host(int32_t n_rows, int32_t n_cols, int64_t nnz,
     A->slots = L.slots;
     A->pipe_product = A->n_groups > 0 &&
                       L.slots >= 32 * int64_t(kWave) * A->n_groups;
+    const bool square = n_rows == n_cols;
 
     auto fail = [&](fs_status code) {
         (void)hipStreamSynchronize(s);
@@ -238,7 +236,8 @@ fs_status create_from_host(int32_t n_rows, int32_t n_cols, int64_t nnz,
         (st = dalloc(&A->d_val, A->slots, acct)) ||
         (st = dalloc(&A->d_col, A->slots, acct)) ||
         (st = dalloc(&A->d_map, nnz, acct)) ||
-        (st = dalloc(&A->d_imap, A->slots, acct)) ||
+        (st = alloc_refresh(A, longest_row(n_rows, h_rp), acct)) ||
+        (st = dalloc(&A->d_diag, square ? n_rows : 0, acct)) ||
         (st = dalloc(&A->d_perm, n_rows, acct)) ||
         (st = dalloc(&A->d_iperm, n_rows, acct)) ||
         (st = dalloc(&A->d_xtmp, n_cols, acct)))
@@ -286,12 +285,50 @@ fs_status create_from_host(int32_t n_rows, int32_t n_cols, int64_t nnz,
         FS_CREATE_HIP(hipMemcpyAsync(A->d_map, L.map.data(),
                                      sizeof(int32_t) * size_t(nnz),
                                      hipMemcpyHostToDevice, s));
-    if (A->slots)
-        FS_CREATE_HIP(hipMemsetAsync(A->d_imap, 0xff,
+    // the inverse map, kept for the value refresh or, as scratch, read by
+    // its smaller form
+    int32_t *inv = nullptr;
+    int2 *counts = nullptr;
+    int64_t scratch_bytes = 0;
+    struct Scratch {
+        int32_t *&i;
+        int2 *&c;
+        ~Scratch() { dfree(i); dfree(c); }
+    } scratch{inv, counts};
+    if (A->slots) {
+        if (A->d_jpos && (st = dalloc(&inv, A->slots, scratch_bytes)))
+            return fail(st);
+        int32_t *const imap = A->d_jpos ? inv : A->d_imap;
+        FS_CREATE_HIP(hipMemsetAsync(imap, 0xff,
                                      sizeof(int32_t) * size_t(A->slots), s));
-    FS_CREATE_HIP(launch_inverse_map(A->d_map, nnz, A->d_imap, s));
-    if ((st = build_refresh_rows(A, h_rp, acct, s))) return fail(st);
-    if ((st = build_stage(A, acct, s))) return fail(st);
+        FS_CREATE_HIP(launch_inverse_map(A->d_map, nnz, imap, s));
+        if (A->d_jpos)
+            FS_CREATE_HIP(launch_refresh_rows(A->d_groups, A->n_groups, L.vec,
+                                              imap, A->d_jpos, A->d_rstart, s));
+    }
+    if (square)
+        FS_CREATE_HIP(launch_diag_slots(A->d_groups, A->n_groups, L.vec,
+                                        A->d_col, A->d_diag, s));
+    std::vector<int2> cnt;
+    std::vector<StageGroup> grp;
+    bool stage = stage_wanted(A);
+    if (stage && (st = dalloc_spare(&A->d_lpat, int64_t(A->n_groups) * kWave,
+                                    scratch_bytes, stage)))
+        return fail(st);
+    if (stage && (st = dalloc_spare(&counts, A->n_groups, scratch_bytes, stage)))
+        return fail(st);
+    if (stage) {
+        if ((st = count_stage(A, A->d_gbase != nullptr, counts, s)))
+            return fail(st);
+        cnt.resize(size_t(A->n_groups));
+        FS_CREATE_HIP(hipMemcpyAsync(cnt.data(), counts,
+                                     sizeof(int2) * cnt.size(),
+                                     hipMemcpyDeviceToHost, s));
+        FS_CREATE_HIP(hipStreamSynchronize(s));
+        if ((st = build_stage(A, cnt, grp, acct, s))) return fail(st);
+    } else {
+        dfree(A->d_lpat);
+    }
     if (n_rows) {
         FS_CREATE_HIP(hipMemcpyAsync(A->d_perm, L.perm.data(),
                                      sizeof(int32_t) * size_t(n_rows),
@@ -366,9 +403,7 @@ fs_status create_on_device(int32_t n_rows, int32_t n_cols, int64_t nnz,
                               hipMemcpyDeviceToHost, s));
     FS_HIP_TRY(hipStreamSynchronize(s));
     FS_TRY(layout_check_rowptr(n_rows, nnz, h_rp.data()));
-    int32_t maxlen = 0;
-    for (int32_t i = 0; i < n_rows; ++i)
-        maxlen = std::max(maxlen, h_rp[size_t(i) + 1] - h_rp[size_t(i)]);
+    const int32_t maxlen = longest_row(n_rows, h_rp.data());
     std::unique_ptr<int32_t[]> h_col;
     auto host_cols = [&]() -> fs_status {
         return fetch_to_host(h_col, colind, nnz, s);
@@ -439,11 +474,16 @@ fs_status create_on_device(int32_t n_rows, int32_t n_cols, int64_t nnz,
         (st = dalloc(&A->d_val, A->slots, acct)) ||
         (st = dalloc(&A->d_col, A->slots, acct)) ||
         (st = dalloc(&A->d_map, nnz, acct)) ||
-        (st = dalloc(&A->d_imap, A->slots, acct)) ||
+        (st = alloc_refresh(A, maxlen, acct)) ||
+        (st = dalloc(&A->d_diag, square ? n_rows : 0, acct)) ||
         (st = dalloc(&A->d_perm, n_rows, acct)) ||
         (st = dalloc(&A->d_iperm, n_rows, acct)) ||
         (st = dalloc(&A->d_xtmp, n_cols, acct)) ||
-        (st = dalloc(&d_lohi, A->n_groups, scratch_bytes)))
+        (st = dalloc(&d_lohi, 2 * int64_t(A->n_groups), scratch_bytes)))
+        return fail(st);
+    bool stage = stage_wanted(A);
+    if (stage && (st = dalloc_spare(&A->d_lpat, int64_t(A->n_groups) * kWave,
+                                    scratch_bytes, stage)))
         return fail(st);
     if (o.dtypes & FS_DT_F32)
         if ((st = dalloc(&A->d_val_f32, A->slots, acct))) return fail(st);
@@ -471,6 +511,8 @@ fs_status create_on_device(int32_t n_rows, int32_t n_cols, int64_t nnz,
                                   sizeof(int32_t) * size_t(A->slots), s));
         FS_DEV_HIP(hipMemsetAsync(A->d_val, 0,
                                   sizeof(double) * size_t(A->slots), s));
+        if (A->d_jpos)
+            FS_DEV_HIP(hipMemsetAsync(A->d_jpos, 0xff, size_t(A->slots), s));
         if (A->d_val_f32)
             FS_DEV_HIP(hipMemsetAsync(A->d_val_f32, 0,
                                       sizeof(float) * size_t(A->slots), s));
@@ -480,13 +522,19 @@ fs_status create_on_device(int32_t n_rows, int32_t n_cols, int64_t nnz,
     }
     FS_DEV_HIP(launch_assign_slots(A->d_groups, A->n_groups, L.vec, A->d_perm,
                                    L.symmetric_relabel ? A->d_iperm : nullptr,
-                                   rowptr, colind, A->d_col, A->d_map, d_lohi,
+                                   rowptr, colind, A->d_col, A->d_map,
+                                   A->d_jpos, A->d_rstart, A->d_diag, d_lohi,
                                    d_flags + 1, s));
     if (square)
         FS_DEV_HIP(launch_band(n_rows, rowptr, colind, A->d_iperm,
                                d_flags + 2, s));
-    std::vector<int2> lohi(size_t(A->n_groups));
-    if (A->n_groups)
+    // counted for 16-bit offsets, which nearly every matrix gets; one copy
+    // brings both halves of the scratch array
+    const size_t ng = size_t(A->n_groups);
+    std::vector<int2> lohi(stage ? 2 * ng : ng), cnt;
+    std::vector<StageGroup> grp;
+    if (stage && (st = count_stage(A, true, d_lohi + ng, s))) return fail(st);
+    if (ng)
         FS_DEV_HIP(hipMemcpyAsync(lohi.data(), d_lohi,
                                   sizeof(int2) * lohi.size(),
                                   hipMemcpyDeviceToHost, s));
@@ -511,7 +559,7 @@ fs_status create_on_device(int32_t n_rows, int32_t n_cols, int64_t nnz,
     // 16-bit offsets when every group's columns span fewer than 65535
     L.index_bits = 32;
     bool fits = o.index_bits == 0 && A->n_groups > 0;
-    for (size_t g = 0; g < lohi.size() && fits; ++g)
+    for (size_t g = 0; g < ng && fits; ++g)
         fits = lohi[g].y - lohi[g].x < 0xffff;
     if (fits) {
         if ((st = dalloc(&A->d_col16, A->slots, acct)) ||
@@ -521,12 +569,24 @@ fs_status create_on_device(int32_t n_rows, int32_t n_cols, int64_t nnz,
                                     A->d_col16, A->d_gbase, s));
         L.index_bits = 16;
     }
-    if (A->slots)
+    if (A->d_imap) {
         FS_DEV_HIP(hipMemsetAsync(A->d_imap, 0xff,
                                   sizeof(int32_t) * size_t(A->slots), s));
-    FS_DEV_HIP(launch_inverse_map(A->d_map, nnz, A->d_imap, s));
-    if ((st = build_refresh_rows(A, h_rp.data(), acct, s))) return fail(st);
-    if ((st = build_stage(A, acct, s))) return fail(st);
+        FS_DEV_HIP(launch_inverse_map(A->d_map, nnz, A->d_imap, s));
+    }
+    if (stage) {
+        cnt.assign(lohi.begin() + int64_t(ng), lohi.end());
+        bool far = false;
+        for (const int2 &n : cnt) far |= n.y < 0;
+        if (far && !fits) {
+            if ((st = count_stage(A, false, d_lohi + ng, s))) return fail(st);
+            FS_DEV_HIP(hipMemcpyAsync(cnt.data(), d_lohi + ng,
+                                      sizeof(int2) * ng,
+                                      hipMemcpyDeviceToHost, s));
+            FS_DEV_HIP(hipStreamSynchronize(s));
+        }
+        if ((st = build_stage(A, cnt, grp, acct, s))) return fail(st);
+    }
     FS_DEV_HIP(launch_value_scatter(vals, A->d_map, nnz, A->d_val,
                                     A->d_val_f32, A->d_val_bf16, s));
     FS_DEV_HIP(hipStreamSynchronize(s));

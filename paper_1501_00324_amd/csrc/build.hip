@@ -97,13 +97,18 @@ __device__ __forceinline__ int layout_col(const int *__restrict__ col,
 // length L costs L * ceil(L / 64) steps.  An entry whose column repeats an
 // earlier entry of its row is a duplicate: the smallest such CSR position
 // is reported through *dup.  The group's smallest and largest column go to
-// lohi (0, -1 for a group without entries).
+// lohi (0, -1 for a group without entries).  What the value refresh and the
+// Jacobi scaling read is known here too: every slot's position in its CSR row
+// (jpos, rows of at most 255 entries; prefilled with 255 = padding), the row
+// starts, and the diagonal's slot of every row (-1: none).
 __global__ __launch_bounds__(kBlock) void k_assign_slots(
     const Group *__restrict__ groups, int ngroups, int V,
     const int *__restrict__ perm, const int *__restrict__ iperm,
     const int *__restrict__ rowptr, const int *__restrict__ col,
     int *__restrict__ slot_col, int *__restrict__ map,
-    int2 *__restrict__ lohi, unsigned long long *__restrict__ dup)
+    uint8_t *__restrict__ jpos, int *__restrict__ rstart,
+    int *__restrict__ diag, int2 *__restrict__ lohi,
+    unsigned long long *__restrict__ dup)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int w0 = __builtin_amdgcn_readfirstlane(
@@ -119,6 +124,7 @@ __global__ __launch_bounds__(kBlock) void k_assign_slots(
             const int k0 = __builtin_amdgcn_readfirstlane(rowptr[orow]);
             const int len =
                 __builtin_amdgcn_readfirstlane(rowptr[orow + 1]) - k0;
+            unsigned long long own = 0;      // lanes that held the diagonal
             for (int e0 = 0; e0 < len; e0 += kWave) {
                 const int e = e0 + lane;
                 const int c = e < len ? layout_col(col, iperm, k0 + e) : INT_MAX;
@@ -145,10 +151,17 @@ __global__ __launch_bounds__(kBlock) void k_assign_slots(
                                      long(ln) * V + s % V;
                     slot_col[idx] = c;
                     map[k0 + e] = int(idx);
+                    if (jpos) jpos[idx] = uint8_t(e);
+                    if (diag && c == G.row0 + rr) diag[c] = int(idx);
                     mn = min(mn, c);
                     mx = max(mx, c);
                     if (rep) atomicMin(dup, (unsigned long long)(k0 + e));
                 }
+                own |= __ballot(c == G.row0 + rr);
+            }
+            if (lane == 0) {
+                if (rstart) rstart[G.row0 + rr] = k0;
+                if (diag && !own) diag[G.row0 + rr] = -1;
             }
         }
 #pragma unroll
@@ -684,13 +697,14 @@ hipError_t launch_assign_slots(const Group *groups, int32_t ngroups,
                                int32_t vec, const int32_t *perm,
                                const int32_t *iperm, const int32_t *rowptr,
                                const int32_t *col, int32_t *slot_col,
-                               int32_t *map, int2 *lohi,
+                               int32_t *map, uint8_t *jpos, int32_t *rstart,
+                               int32_t *diag, int2 *lohi,
                                unsigned long long *dup, hipStream_t s)
 {
     if (ngroups == 0) return hipSuccess;
     hipLaunchKernelGGL(k_assign_slots, dim3(wave_grid(ngroups)), dim3(kBlock),
                        0, s, groups, ngroups, vec, perm, iperm, rowptr, col,
-                       slot_col, map, lohi, dup);
+                       slot_col, map, jpos, rstart, diag, lohi, dup);
     return hipGetLastError();
 }
 

@@ -422,7 +422,8 @@ hipError_t launch_assign_slots(const Group *groups, int32_t ngroups,
                                int32_t vec, const int32_t *perm,
                                const int32_t *iperm, const int32_t *rowptr,
                                const int32_t *col, int32_t *slot_col,
-                               int32_t *map, int2 *lohi,
+                               int32_t *map, uint8_t *jpos, int32_t *rstart,
+                               int32_t *diag, int2 *lohi,
                                unsigned long long *dup, hipStream_t s);
 hipError_t launch_offsets16(const Group *groups, int32_t ngroups,
                             const int32_t *slot_col, const int2 *lohi,
