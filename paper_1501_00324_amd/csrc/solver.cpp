@@ -187,9 +187,10 @@ template <class T>
 fs_status ensure_cap(T *&p, int32_t &cap, int32_t want)
 {
     if (want <= cap) return FS_OK;
-    dfree(p);
     int64_t dummy = 0;
-    int32_t c = std::max(want, 2 * cap);
+    const int32_t c = std::max(want, 2 * cap);
+    dfree(p);
+    cap = 0;                   // (nothing is held if the next line fails)
     FS_TRY(dmalloc(reinterpret_cast<void **>(&p), sizeof(T) * size_t(c),
                    dummy));
     cap = c;

@@ -1,7 +1,8 @@
-"""csr_create when device memory is short: an allocation that fails either
+"""When device memory is short.  csr_create: an allocation that fails either
 fails the creation with FS_E_OOM or, for the arrays of the staged products,
-leaves a handle whose products gather per slot.  Every allocation of a build
-fails once; a child process resolves hipMalloc to a counting one."""
+leaves a handle whose products gather per slot.  Solves: a handle whose
+workspace could not grow solves on.  Every allocation fails once; a child
+process resolves hipMalloc to a counting one."""
 import os
 import subprocess
 import sys
@@ -75,16 +76,65 @@ print("DONE")
 """
 
 
-def test_every_allocation_fails_once(tmp_path):
-    note("scarce memory")
+SOLVES = r"""
+import ctypes, sys
+import numpy as np, torch
+torch.cuda.init()
+shim = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+import paper_1501_00324_amd as fs
+import workloads as W
+from tests.gpu_util import make, dev, host
+fs.load(build_if_missing=False)
+A = W.tet_p1(8, "elastic", seed=(92, 0), bc="x0")
+g = np.random.default_rng(1)
+B2, B16 = dev(g.uniform(-1, 1, (A.n_rows, 2))), dev(g.uniform(-1, 1, (A.n_rows, 16)))
+ref2, ref16 = (host(fs.cg_solve_multi(make(A), B)[0]) for B in (B2, B16))
+kinds = ""
+for n in range(40):
+    M = make(A)
+    X = fs.cg_solve_multi(M, B2)[0]
+    assert np.array_equal(host(X), ref2)
+    shim.arm(n)
+    try:
+        X = fs.cg_solve_multi(M, B16)[0]
+        done = shim.count() <= n
+    except fs.FsError as e:
+        assert e.status == fs.FS_E_OOM, e
+        done = False
+        kinds += "E"
+    finally:
+        shim.arm(-1)
+    # the handle's kept arrays grew, or a part of them: smaller, then larger
+    for B, ref in ((B2, ref2), (B2, ref2), (B16, ref16), (B2, ref2)):
+        assert np.array_equal(host(fs.cg_solve_multi(M, B)[0]), ref), n
+    if done:
+        break
+assert done and kinds.count("E") >= 8, kinds
+print("DONE")
+"""
+
+
+def run_child(tmp_path, code):
     src, lib = tmp_path / "shim.c", tmp_path / "shim.so"
     src.write_text(SHIM)
     subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(lib), str(src), "-ldl"], check=True)
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    r = subprocess.run([sys.executable, "-c", textwrap.dedent(CHILD), str(lib)], cwd=root, capture_output=True, text=True,
+    r = subprocess.run([sys.executable, "-c", textwrap.dedent(code), str(lib)], cwd=root, capture_output=True, text=True,
                        timeout=100)
     assert r.returncode == 0 and "DONE" in r.stdout, r.stdout[-2000:] + r.stderr[-2000:]
-    for line in r.stdout.splitlines():
+    return r.stdout
+
+
+def test_solves_around_a_failed_growth(tmp_path):
+    """A handle's kept launch arrays grow for more columns; where one of them
+    fails, the next solves find arrays that hold what they need."""
+    note("scarce memory: solves")
+    run_child(tmp_path, SOLVES)
+
+
+def test_every_allocation_fails_once(tmp_path):
+    note("scarce memory")
+    for line in run_child(tmp_path, CHILD).splitlines():
         if line.startswith("KINDS"):
             # list positions, columns, groups, patterns (the host build also counts apart)
             assert line.split()[-1].count("s") >= 4, line
