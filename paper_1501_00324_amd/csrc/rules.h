@@ -2,6 +2,7 @@
 // without HIP types.
 #pragma once
 
+#include <array>
 #include <cstdint>
 
 namespace fs {
@@ -103,6 +104,17 @@ inline int32_t stage_forms(int32_t widest, double columns, double slots,
 {
     if (widest > kStageMax || columns > kStageMost * slots) return 0;
     return widest <= kStageMaxOwn || rows >= kStageShared * patterns ? 2 : 1;
+}
+
+// Batch shape that a timed workgroup choice of cg_solve_batch_wg is kept for.
+// `held`: every member's slots fit in registers, where 1024 threads stand for
+// the kernel that holds them -- a choice timed with one of the two kernels
+// says nothing about the other.
+typedef std::array<int64_t, 7> WgKey;
+inline WgKey wg_key(int64_t dev, int64_t m, int64_t rows, int64_t nnz,
+                    int64_t parts, uint64_t kinds, bool held)
+{
+    return {dev, m, rows, nnz, parts, int64_t(kinds), held ? 1 : 0};
 }
 
 }  // namespace fs

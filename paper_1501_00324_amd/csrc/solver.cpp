@@ -4,7 +4,6 @@
 // true-residual confirmation with residual replacement), mixed-precision
 // iterative refinement, and the cg_solve* entry points.
 #include <algorithm>
-#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -1218,7 +1217,7 @@ constexpr int32_t kWgCandidates[] = {256, 512, 1024};
 // LDS where they fit; 1: z alone, which leaves room for more workgroups
 // per compute unit)
 std::mutex g_wg_mu;
-std::map<std::array<int64_t, 6>, int32_t> g_wg_tuned;
+std::map<WgKey, int32_t> g_wg_tuned;
 
 // Work space of cg_solve_batch_wg per device, kept between calls and grown
 // to the largest batch (held until the process ends: freeing it from a
@@ -1412,8 +1411,7 @@ extern "C" fs_status cg_solve_batch_wg(int32_t m, const fs_csr_t *A,
         // with less in LDS can be, which the timed runs tell
         int32_t choice = o.wg_threads ? o.wg_threads * 4 + 2
                          : all_held && m <= kWgUnits ? 1024 * 4 + 2 : 0;
-        const std::array<int64_t, 6> key = {dev, m, rows, nnz, parts,
-                                            int64_t(kinds)};
+        const WgKey key = wg_key(dev, m, rows, nnz, parts, kinds, all_held);
         if (!choice) {
             std::lock_guard<std::mutex> lk(g_wg_mu);
             auto it = g_wg_tuned.find(key);

@@ -47,3 +47,13 @@ def test_rows_too_short_to_stage(tmp_path):
     for (int w : {1, 3, 4, 5, 7}) std::printf("%d ", int(stage_pays(64.0 * w, 64.0)));
 """)
     assert out == ["0", "0", "0", "1", "1"]
+
+
+def test_workgroup_choice_is_kept_per_kernel(tmp_path):
+    """Batches of the same totals, of which one holds its slots in registers,
+    are timed apart."""
+    out = run_cpp(tmp_path, ["rules.h"], r"""
+    const WgKey a = wg_key(0, 300, 634800, 4400000, 9, 7, true), b = wg_key(0, 300, 634800, 4400000, 9, 7, false);
+    std::printf("%d %d\n", int(a == b), int(a == wg_key(0, 300, 634800, 4400000, 9, 7, true)));
+""")
+    assert out == ["0", "1"]
