@@ -308,8 +308,12 @@ typedef struct fs_cg_opts {
     int32_t precond;      /* FS_PC_*; default JACOBI                         */
     int32_t precision;    /* FS_PREC_*; default F64                          */
     double inner_rtol;    /* IR: inner solve tolerance; 0 = default 1e-2    */
-    int32_t check_every;  /* iterations between host convergence checks
-                             (one captured graph); 0 = default 32           */
+    int32_t check_every;  /* the most iterations between host convergence
+                             checks; 0 = default 32.  A multiple of 4 lets
+                             the solve check sooner where its rate of
+                             convergence says that fewer are left (chunks
+                             of 4 and 16 iterations, one kept graph each);
+                             any other value is taken as it is              */
     int32_t x0_zero;      /* 1: start from x = 0 and ignore x on input      */
     int32_t use_graph;    /* 1: replay chunks as HIP graphs (default 1)    */
     int32_t max_outer;    /* IR: refinement steps; 0 = default 50           */
@@ -335,8 +339,13 @@ typedef struct fs_cg_opts {
                              and with z = D^-1 r alone there (more
                              workgroups per compute unit), timed on the
                              first call for a batch shape and remembered
-                             for the process (the results do not depend on
-                             the choice)                                    */
+                             for the process.  A batch whose matrices all
+                             have one lane per row, at most 8 slots per row
+                             and 48 row groups, with the vectors in LDS,
+                             keeps its slots in registers in the place of
+                             1024 threads (768 threads); up to 256 such
+                             systems, 0 takes that form untimed.  (The
+                             results do not depend on the choice)           */
     int32_t reserved[2];  /* must be zero                                    */
 } fs_cg_opts;
 

@@ -501,10 +501,12 @@ __device__ __forceinline__ void coop_group_pair(const Group &g, int lane,
 // the gathers are latency bound; KM = 1 holds 7 waves (at 8 the FP64
 // product spills a register and the solve slows by 13%), KM = 8 and 16
 // hold 4 (128 registers), except the float KM = 16 product, which needs
-// more registers and keeps 3.
+// more registers and keeps 3.  Staged products have none (their LDS bounds
+// them), the matrix cores' that of tiles.h.
 constexpr int spmm_dot_min_waves(int km, int st_bytes, bool staged)
 {
-    return staged ? (km > 1 ? tile_waves(km) : 1) : km == 16 && st_bytes == 4 ? 3 : km >= 8 ? 4 : km == 1 ? 7 : 1;
+    if (staged) return km > 1 ? tile_waves(km) : 1;
+    return km == 16 && st_bytes == 4 ? 3 : km >= 8 ? 4 : km == 1 ? 7 : 1;
 }
 
 // Q = A P for every column with per-block partials of p_c . q_c.
@@ -528,16 +530,17 @@ __global__ __launch_bounds__(kBlock, spmm_dot_min_waves(KM, int(sizeof(ST)), STG
     with_narrow(S.gbase != nullptr, [&](auto nt) {
         constexpr bool N = decltype(nt)::value;
         if constexpr (STG && KM > 1) {
+            // (a buffer for each of the two column widths: 53 KB of LDS, which
+            // leave three wavefronts per SIMD)
             __shared__ TileBuf tiles[kWavesPerBlock];
-            constexpr int NP = tile_parts<KM>();
-            for (int i = g0 * NP + int(threadIdx.x >> 6); i < g1 * NP;
+            static_assert(tile_parts<KM>() == 1, "one work item per group");
+            for (int i = g0 + int(threadIdx.x >> 6); i < g1;
                  i += kWavesPerBlock) {
-                const int g = __builtin_amdgcn_readfirstlane(i / NP);
+                const int g = __builtin_amdgcn_readfirstlane(i);
                 const Group gd = load_group(gbl(S.groups), g);
                 tile_group<V, KM, N>(
                     gd, g, lane, val, cst, N ? load_gbase(gbl(S.gbase), g) : 0,
-                    gbl(S.st.lpat), P, k, k, tiles[threadIdx.x >> 6],
-                    __builtin_amdgcn_readfirstlane(i % NP),
+                    gbl(S.st.lpat), P, k, k, tiles[threadIdx.x >> 6], 0,
                     [&](int rg, int q, double v) {
                         const long e = long(gd.row0 + rg) * k + q;
                         Q[e] = v;

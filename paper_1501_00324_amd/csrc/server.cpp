@@ -309,7 +309,9 @@ fs_status step(fs_server *S)
         std::vector<CgSys *> syss;
         for (Request *R : mem[cls]) syss.push_back(&R->sys);
         if (syss != B.members || joined[cls]) {
-            // membership changed: new descriptors (the graph goes too)
+            // membership changed: new descriptors; the graph goes with
+            // the launch's shape (batch_build), and the next chunk runs
+            // without one
             B.members = syss;
             B.vt = VT_F64;
             B.st = ST_F64;

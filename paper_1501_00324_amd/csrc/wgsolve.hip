@@ -150,13 +150,15 @@ __device__ __forceinline__ void part_totals(const double *buf, int np,
 // Where the vectors live (MODE): 0 all in global memory; 1 z in LDS; 2 z,
 // x, r, p and q in LDS (x copied in at the start and out at the end; b and
 // D^-1, which the iterations only read, stay in global memory and L2); 3
-// nothing is read from L2 in an iteration: a wavefront holds the slots of
-// its four row groups (one lane per row, up to kHeldWidth slots), p and q in
-// registers, and z, x, r and D^-1 are in LDS.  Four groups are two units of
-// the product step and, with 64 rows each, one of the vector step, so the
-// sums are those of the other modes.  (An iteration waited three times for
-// L2: descriptors, slots, D^-1.  64 systems of 2,116 rows: 7.1 us per
-// iteration in mode 2.)
+// a wavefront holds the slots of its four row groups (one lane per row, up to
+// kHeldWidth slots), p and q in registers, and z, x, r and D^-1 are in LDS.
+// Four groups are two units of the product step and, with 64 rows each, one
+// of the vector step, so the sums are those of the other modes.  (An
+// iteration of mode 2 waits three times for L2: descriptors, slots, D^-1; 64
+// systems of 2,116 rows take it 7.1 us per iteration, mode 3 4.0.)  The
+// registers do not hold all of it: of the values of a wavefront's first group
+// the compiler keeps eight in scratch memory (31 words per lane), which every
+// iteration reads back, one wait each.
 constexpr int kHeldWidth = kWgHeldWidth;
 constexpr int kHeldGroups = 4;
 static_assert(kHeldGroups == kCU && kHeldGroups == 2 * kGU,
@@ -585,8 +587,9 @@ __global__ __launch_bounds__(BS) void k_cg_wg(const WgSys *__restrict__ sys,
     else wg_by_stream<0>(S, a, lds);
 }
 
-// Every system in mode 3: 12 wavefronts, whose 168 registers hold four
-// groups (1024 threads leave 128, which spill them).
+// Every system in mode 3: 12 wavefronts of 168 registers, which hold four
+// groups but for 124 bytes a lane (1024 threads leave 128 registers, with
+// which a call took 353 us against 281: 64 systems of 2,116 rows).
 __global__ __launch_bounds__(kWgHeldThreads) void k_cg_wg_held(
     const WgSys *__restrict__ sys, const WgArgs a)
 {
