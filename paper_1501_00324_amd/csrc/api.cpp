@@ -142,20 +142,23 @@ fs_status build_stage(fs_csr *A, const std::vector<int2> &cnt,
     const size_t ng = cnt.size();
     const bool narrow = A->d_gbase != nullptr;
     grp.resize(ng);
-    int64_t loc = 0, list = 0, patterns = 0;
+    int64_t loc = 0, list = 0, patterns = 0, lines = 0;
     int32_t most = 0;
     for (size_t g = 0; g < ng; ++g) {
         const int32_t wl = A->host.groups[g].width_lt;
-        const int32_t per = cnt[g].x << (wl >> 24), nd = cnt[g].y;
+        const int32_t np = cnt[g].x & 255, nd = cnt[g].y;
+        const int32_t per = np << (wl >> 24);
         most = nd < 0 ? INT32_MAX : std::max(most, nd);
         if (most > kStageMax) break;
         grp[g] = StageGroup{int32_t(loc), per, int32_t(list), nd};
         loc += int64_t(per) * (((wl & 0xffffff) + 3) / 4);
         list += nd;
-        patterns += cnt[g].x;
+        patterns += np;
+        lines += cnt[g].x >> 8;
     }
     const int32_t pays = stage_forms(most, double(list), double(A->slots),
-                                     double(A->n_rows), double(patterns));
+                                     double(A->n_rows), double(patterns),
+                                     A->host.vec, double(lines));
     int64_t bytes = int64_t(ng) * kWave;      // d_lpat
     bool have = pays > 0;
     char *cols = nullptr;
@@ -174,8 +177,8 @@ fs_status build_stage(fs_csr *A, const std::vector<int2> &cnt,
     FS_HIP_TRY(launch_stage_lists(A->d_groups, A->n_groups, A->host.vec,
                                   A->d_col, A->d_gbase, A->d_sgrp, A->d_lpat,
                                   A->d_loc, A->d_scols, s));
-    A->stage_max = std::max(most, 1);
-    A->stage_f64 = pays == 2 ? A->stage_max : 0;
+    for (int vt : {VT_F64, VT_F32, VT_BF16})
+        A->stage[vt] = pays >> vt & 1 ? std::max(most, 1) : 0;
     double lanes = 0.0;
     for (int i = 0; i < 7; ++i)
         lanes += double(A->host.groups_by_lanes[i]) * (1 << i);
@@ -899,7 +902,9 @@ fs_status csr_info(fs_csr_t A, fs_csr_stats *st)
 int32_t fs_product_forms(fs_csr_t A)
 {
     if (!A) return 0;
-    return (A->d_sgrp ? kFormStaged : 0) | (A->stage_f64 ? kFormStagedF64 : 0) |
+    return (A->stage[VT_F32] ? kFormStaged : 0) |
+           (A->stage[VT_F64] ? kFormStagedF64 : 0) |
+           (A->stage[VT_BF16] ? kFormStagedBf16 : 0) |
            (A->refresh_width > 0 ? kFormRefreshTiles : 0) | A->tiles << kFormTiles;
 }
 

@@ -265,8 +265,10 @@ __device__ __forceinline__ bool column_bitmap(const int *__restrict__ cols,
 // Row patterns and distinct columns of a group.  Rows whose columns equal
 // the previous row's share its pattern, up to four rows per pattern (the
 // row tile of the multi-column products); lane j of a row of pattern p
-// reads position entry p * T + j.  counts[g] = {patterns, distinct columns
-// or -1}.
+// reads position entry p * T + j.  counts[g] = {patterns + 256 * lines,
+// distinct columns or -1}; lines: what the group's gathers by slot would
+// touch, as runs of lanes whose columns share 128 bytes (rows of one lane;
+// else every lane counts).
 __global__ __launch_bounds__(kWave) void k_stage_count(
     const Group *__restrict__ groups, int V, const int *__restrict__ slot_col,
     int span, uint8_t *__restrict__ lpat, int2 *__restrict__ counts)
@@ -277,11 +279,13 @@ __global__ __launch_bounds__(kWave) void k_stage_count(
     const int *cols = slot_col + long(G.base64) * kWave;
     const int width = G.width_lt & 0xffffff, lt = G.width_lt >> 24;
     const int T = 1 << lt, row = lane >> lt;
-    int differs = row == 0;
+    int differs = row == 0, lines = 0;
     for (int s = 0; s < width; ++s) {
         const int c = cols[(s / V) * kWave * V + lane * V + s % V];
         const int up = __shfl(c, lane >= T ? lane - T : lane, kWave);
         differs |= c != up;
+        lines += __popcll(__ballot(
+            c >= 0 && (T > 1 || lane == 0 || c >> 4 != up >> 4)));
     }
     for (int o = 1; o < T; o <<= 1) differs |= __shfl_xor(differs, o, kWave);
     const unsigned long long starts = __ballot(differs != 0);
@@ -303,7 +307,8 @@ __global__ __launch_bounds__(kWave) void k_stage_count(
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) nd += __shfl_xor(nd, o, kWave);
     }
-    if (lane == kWave - 1) counts[g] = make_int2(p + 1, nd);
+    if (lane == kWave - 1)
+        counts[g] = make_int2(p + 1 + (min(lines, 0x7fffff) << 8), nd);
 }
 
 // The group's column list (ascending) and every pattern's positions in it,

@@ -1527,19 +1527,21 @@ hipError_t launch_spmv_lowp(const fs_csr *A, int32_t dtype, const float *x,
         const VT *val = dtype == FS_DT_F32
                             ? reinterpret_cast<const VT *>(A->d_val_f32)
                             : reinterpret_cast<const VT *>(A->d_val_bf16);
-        if (A->d_sgrp) {
+        const int32_t stage =
+            A->stage[dtype == FS_DT_F32 ? VT_F32 : VT_BF16];
+        if (stage) {
             const size_t lds =
-                sizeof(float) * size_t(A->stage_max + 1) * kWavesPerBlock;
+                sizeof(float) * size_t(stage + 1) * kWavesPerBlock;
             if (A->d_gbase)
                 hipLaunchKernelGGL((k_spmv_staged<VT, float, V, false, true>),
                                    grid, dim3(kBlock), lds, s, A->d_groups,
                                    A->n_groups, val, stage_of(A),
-                                   A->stage_max, x, y, nullptr);
+                                   stage, x, y, nullptr);
             else
                 hipLaunchKernelGGL((k_spmv_staged<VT, float, V, false, false>),
                                    grid, dim3(kBlock), lds, s, A->d_groups,
                                    A->n_groups, val, stage_of(A),
-                                   A->stage_max, x, y, nullptr);
+                                   stage, x, y, nullptr);
             return;
         }
         if (A->d_col16)

@@ -115,7 +115,7 @@ constexpr int64_t kLocCached = int64_t(56) << 20;
 // Bits of fs_product_forms (api.cpp); from bit kFormTiles on the column
 // classes on the matrix cores.
 constexpr int32_t kFormStaged = 1, kFormStagedF64 = 2, kFormRefreshTiles = 4,
-                  kFormTiles = 8;
+                  kFormTiles = 8, kFormStagedBf16 = 1 << 16;
 
 // ------------------------------------------------- batched CG engine state
 // Status of one right-hand side.
@@ -157,8 +157,7 @@ struct SysDesc {
     int32_t hist_cap, pad2;      //   column), or NULL: not recorded
 };
 
-// Value / vector type classes of a launch.
-enum { VT_F64 = 0, VT_F32 = 1, VT_BF16 = 2 };
+// Vector type classes of a launch (value types: rules.h).
 enum { ST_F64 = 0, ST_F32 = 1 };
 
 struct EngineLaunch {            // one batched launch shape
@@ -310,9 +309,9 @@ struct fs_csr {
     uint16_t *d_loc = nullptr;
     uint8_t *d_lpat = nullptr;
     void *d_scols = nullptr;
-    int32_t stage_max = 0;         // distinct columns of the widest group
-    int32_t stage_f64 = 0;         // the same, 0: FP64 gathers per slot
-                                   //   (rules.h: stage_forms)
+    int32_t stage[3] = {0, 0, 0};  // by value type (VT_*): distinct columns
+                                   //   of the widest group, 0: the product
+                                   //   gathers per slot (rules.h: stage_forms)
     // column classes whose products run on the matrix cores (rules.h:
     // tile_classes)
     int32_t tiles = 0;

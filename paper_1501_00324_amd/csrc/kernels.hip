@@ -167,17 +167,17 @@ void spmv_go(const fs_csr *A, const double *x, double *y,
     const void *col = N ? static_cast<const void *>(A->d_col16)
                         : static_cast<const void *>(A->d_col);
     const size_t lds =
-        sizeof(double) * size_t(A->stage_max + 1) * kWavesPerBlock;
-    if (A->stage_f64 && A->stream_loc)
+        sizeof(double) * size_t(A->stage[VT_F64] + 1) * kWavesPerBlock;
+    if (A->stage[VT_F64] && A->stream_loc)
         hipLaunchKernelGGL((k_spmv_staged<double, double, V, S, N, true>),
                            dim3(spmv_blocks(A->n_groups)), dim3(kBlock), lds,
                            s, A->d_groups, A->n_groups, A->d_val, stage_of(A),
-                           A->stage_max, x, y, yperm);
-    else if (A->stage_f64)
+                           A->stage[VT_F64], x, y, yperm);
+    else if (A->stage[VT_F64])
         hipLaunchKernelGGL((k_spmv_staged<double, double, V, S, N>),
                            dim3(spmv_blocks(A->n_groups)), dim3(kBlock), lds,
                            s, A->d_groups, A->n_groups, A->d_val, stage_of(A),
-                           A->stage_max, x, y, yperm);
+                           A->stage[VT_F64], x, y, yperm);
     else if (A->pipe_product)
         hipLaunchKernelGGL((k_spmv_f64<V, S, N, true>),
                            dim3(spmv_blocks(A->n_groups)), dim3(kBlock), 0, s,

@@ -58,10 +58,12 @@ inline int32_t tile_classes(double rows, double patterns, double slots,
            (mean_lanes <= kTileLanes ? wide : 0);
 }
 
-// Which single-column products are staged (internal.h: StageGroup), by
-// distinct columns: 0 none, 1 those on float vectors, 2 FP64 too.  A staged
-// group gathers each of its columns once instead of once per slot, and reads
-// its list on top.  us per product, gathers per slot / staged (rows of one
+// Value type classes of a launch.
+enum { VT_F64 = 0, VT_F32 = 1, VT_BF16 = 2 };
+
+// Which single-column products are staged (internal.h: StageGroup), bits by
+// value type.  A staged group gathers each of its columns once instead of once
+// per slot, and reads its list on top.  us per product, gathers per slot / staged (rows of one
 // length along a band unless a mesh is named; 6 M to 18 M slots):
 //
 //                                    FP64          FP32          BF16
@@ -89,21 +91,36 @@ inline int32_t tile_classes(double rows, double patterns, double slots,
 // rows that share them in threes: one copy of the positions for three
 //   1280 (153)                       47.5 / 45.6   40.4 / 30.7   30.2 / 21.5
 //   1900 (228, past the LDS limit)   73.5 / 66.2   56.1 / 46.4   41.4 / 32.0
+// lines of 128 bytes that the 64 lanes of a slot touch, Q1 Laplacian, in
+// natural numbering (5.5: whole runs of neighbours) and reverse Cuthill-McKee
+// (8 to 12); short rows read by single slots gain either way
+//   80^3 natural                     25.7 / 27.7   16.9 / 17.5   12.8 / 13.5
+//   96^3 natural                     45.1 / 43.7   26.7 / 28.0   20.1 / 22.3
+//   110^3 natural                    69.9 / 69.8   38.8 / 39.0   29.2 / 30.5
+//   126^3 natural                   106.3 / 101.6  58.6 / 55.9   43.5 / 42.3
+//   70^3                             19.5 / 19.6   15.0 / 12.5   11.6 /  9.5
+//   90^3                             37.7 / 37.2   25.9 / 24.0   19.5 / 18.9
 constexpr int32_t kStageMax = 1280;     // columns of the widest group,
 constexpr int32_t kStageMaxOwn = 1023;  //   FP64 with rows of their own
 constexpr double kStageShared = 1.5;    // rows per pattern from which rows
                                         //   count as sharing
 constexpr double kStageMost = 0.45;     // columns per slot
 constexpr double kStageSlots = 4.5;     // mean slots per lane
+constexpr double kStageLines = 7.5;     // BF16 with rows of their own, read
+                                        //   by pairs: lines per slot
 inline bool stage_pays(double slots, double lanes)
 {
     return slots >= kStageSlots * lanes;
 }
 inline int32_t stage_forms(int32_t widest, double columns, double slots,
-                           double rows, double patterns)
+                           double rows, double patterns, int32_t vec,
+                           double lines)
 {
     if (widest > kStageMax || columns > kStageMost * slots) return 0;
-    return widest <= kStageMaxOwn || rows >= kStageShared * patterns ? 2 : 1;
+    const bool shared = rows >= kStageShared * patterns;
+    const bool f64 = shared || widest <= kStageMaxOwn;
+    const bool bf16 = shared || vec == 1 || 64 * lines >= kStageLines * slots;
+    return 1 << VT_F32 | (f64 ? 1 << VT_F64 : 0) | (bf16 ? 1 << VT_BF16 : 0);
 }
 
 // Batch shape that a timed workgroup choice of cg_solve_batch_wg is kept for.

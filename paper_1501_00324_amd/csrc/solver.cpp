@@ -217,7 +217,7 @@ fs_status batch_build(Batch &B, hipStream_t s)
                                : static_cast<const void *>(A->d_col);
         d.gbase = A->d_col16 ? A->d_gbase : nullptr;
         d.st = stage_of(A);
-        const int32_t widest = S.st == ST_F64 ? A->stage_f64 : A->stage_max;
+        const int32_t widest = A->stage[S.vt];
         all_staged &= widest > 0 || A->n_groups == 0;
         all_tiles &= A->n_groups == 0 || runs_tiles(A, S.k);
         stage = std::max(stage, widest);

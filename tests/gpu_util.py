@@ -41,8 +41,8 @@ def assert_spmv_close(y, y_ref, scale, what=""):
         what, bad.sum(), np.nonzero(bad)[0][:5])
 
 
-# single-column products staged on float vectors, in FP64; refresh by rows
-STAGED, STAGED64, REFRESH_TILES = 1, 2, 4
+# single-column products staged in FP32, FP64, BF16; refresh by rows
+STAGED, STAGED64, STAGED16, REFRESH_TILES = 1, 2, 1 << 16, 4
 # products of up to 4, 8 and 16 columns on the matrix cores
 TILES4, TILES8, TILES16 = 1 << 10, 1 << 11, 1 << 12
 TILES = TILES4 | TILES8 | TILES16

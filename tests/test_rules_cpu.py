@@ -26,19 +26,26 @@ def test_tile_classes(tmp_path, what, rows, patterns, slots, lanes, classes):
     assert out == [str(classes)], what
 
 
-@pytest.mark.parametrize("what,widest,columns,slots,rows,patterns,forms", [
-    ("P1 elasticity", 400, 9e5, 9e6, 2e5, 7e4, 2),
-    ("P1 Laplacian", 300, 4e5, 1e6, 7e4, 7e4, 2),
-    ("45 % of the slots", 300, 4.5e5, 1e6, 7e4, 7e4, 2),
-    ("over it", 300, 4.6e5, 1e6, 7e4, 7e4, 0),
-    ("rows of their own, 32 KB of LDS", 1023, 1e5, 1e6, 2e4, 2e4, 2),
-    ("over it", 1024, 1e5, 1e6, 2e4, 2e4, 1),
-    ("shared rows", 1280, 1e5, 1e6, 2e4, 1e4, 2),
-    ("over the limit", 1281, 1e5, 1e6, 2e4, 1e4, 0),
+F64, F32, BF16 = 1, 2, 4
+ALL = F64 | F32 | BF16
+
+
+@pytest.mark.parametrize("what,widest,columns,slots,rows,patterns,vec,lines,forms", [
+    ("P1 elasticity", 400, 9e5, 9e6, 2e5, 7e4, 2, 8.5, ALL),
+    ("P1 elasticity in runs", 400, 9e5, 9e6, 2e5, 7e4, 2, 5, ALL),
+    ("P1 Laplacian", 300, 4e5, 1e6, 7e4, 7e4, 1, 5, ALL),
+    ("Q1 Laplacian", 300, 4e5, 1e6, 4e4, 4e4, 2, 8, ALL),
+    ("in natural numbering", 300, 4e5, 1e6, 4e4, 4e4, 2, 7, F64 | F32),
+    ("45 % of the slots", 300, 4.5e5, 1e6, 7e4, 7e4, 2, 64, ALL),
+    ("over it", 300, 4.6e5, 1e6, 7e4, 7e4, 2, 64, 0),
+    ("rows of their own, 32 KB of LDS", 1023, 1e5, 1e6, 2e4, 2e4, 2, 64, ALL),
+    ("over it", 1024, 1e5, 1e6, 2e4, 2e4, 2, 64, F32 | BF16),
+    ("shared rows", 1280, 1e5, 1e6, 2e4, 1e4, 2, 64, ALL),
+    ("over the limit", 1281, 1e5, 1e6, 2e4, 1e4, 2, 64, 0),
 ])
-def test_stage_forms(tmp_path, what, widest, columns, slots, rows, patterns, forms):
-    out = run_cpp(tmp_path, ["rules.h"], 'std::printf("%%d\\n", stage_forms(%d, %s, %s, %s, %s));' % (
-        widest, float(columns), float(slots), float(rows), float(patterns)))
+def test_stage_forms(tmp_path, what, widest, columns, slots, rows, patterns, vec, lines, forms):
+    out = run_cpp(tmp_path, ["rules.h"], 'std::printf("%%d\\n", stage_forms(%d, %s, %s, %s, %s, %d, %s));' % (
+        widest, float(columns), float(slots), float(rows), float(patterns), vec, lines * slots / 64))
     assert out == [str(forms)], what
 
 
