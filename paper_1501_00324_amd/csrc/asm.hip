@@ -69,7 +69,8 @@ __global__ __launch_bounds__(kBlock) void k_assemble(
 
 // Place in LDS of a group's slot: one double of padding per 64, so that the
 // entries of a row, which lie 64 or 128 doubles apart, fall into different
-// banks (unpadded, conflicts took 62% of the LDS cycles).
+// banks (unpadded, conflicts took 62% of the LDS cycles; now 47% of
+// asm_matrix's and 34% of asm_system's).
 __device__ __forceinline__ int lds_place(int slot) { return slot + (slot >> 6); }
 __device__ __forceinline__ uint16_t lds_place(uint16_t off)
 {
@@ -136,12 +137,14 @@ __global__ __launch_bounds__(kBlock) void k_interleave_offsets(
 //
 // BIG: element matrices larger together than the last-level cache.  An
 // element is read by the groups of all its nodes, about a level of the
-// locality order apart; with one contiguous range per XCD the eight windows
-// do not fit that cache and elements are fetched again (3.53 GB fetched for
-// 2.3 GB on the P1 elasticity 64^3 mesh), so the XCDs take chunks of 32
-// groups side by side, and the values stream out past the caches.  Smaller
-// data keeps the contiguous ranges (P1 Laplacian 70^3, 252 MB: 203 us, 218
-// in chunks).
+// locality order apart, which an L2 does not hold: the L2s read
+// 3.6 GB for 2.3 GB of elements and plan (P1 elasticity 64^3, asm_system).
+// With one contiguous range per XCD the eight windows are eight places of
+// the element data; in chunks of 32 groups side by side the XCDs read one
+// place of it at a time, and the values stream out past the caches.  The
+// L2s read as much either way (3.64 and 3.61 GB), but it comes sooner:
+// 646 us in contiguous ranges, 578 in chunks.  Smaller data keeps the
+// contiguous ranges (P1 Laplacian 70^3, 252 MB: 203 us, 218 in chunks).
 template <int U, bool WR, bool ORD, int EL, bool BIG, bool LAT>
 __global__ __launch_bounds__(kBlock) void k_assemble_lds(
     const int4 *__restrict__ gdesc, const int4 *__restrict__ bdesc,

@@ -362,7 +362,7 @@ __device__ __forceinline__ void coop_group(const Group &g, int lane,
 // row, 128/KM rows per round, KM/2 rounds per slot, and 16-byte X loads.
 // The texture address unit processes a gather instruction at a fixed rate of
 // lanes per cycle whatever each lane loads, and the KM = 16 product is bound
-// by it (counters: address unit busy 88% of the kernel); two columns per
+// by it (counters: address unit busy 85% of the kernel); two columns per
 // lane halve its gather instructions.  Every (row, column) sum is formed
 // exactly as in coop_group (each slot lane's entries in order, then the same
 // tree over a row's lanes), and the values are handed to the lanes that

@@ -12,10 +12,11 @@ namespace {
 // to four rows of a pattern times KM columns of Y are v_mfma_f64_4x4x4
 // tiles, A(row, entry) X(column of entry, :).  What bounds the multi-column
 // products is the address unit, which takes four lanes a cycle whatever they
-// load (counters: 82-88% busy, both for coop_group and for these tiles with
-// 8-byte gathers): so X is read once per (pattern, entry) instead of once
-// per (row, entry), and 16 bytes a lane -- two columns, one for each of two
-// instructions that share their A operand.
+// load (counters: 85% busy in coop_group with 16 columns): so X is read once
+// per (pattern, entry) instead of once per (row, entry), and 16 bytes a lane
+// -- two columns, one for each of two instructions that share their A operand
+// (69% busy with 16 columns, 77% with 8 and 75% with 4, whose lanes take 8
+// bytes: P1 elasticity 64^3).
 //
 // Lane l of the instruction is block b = l / 4 % 4; row (A) and column (B, D)
 // l % 4 of the block; entry (A, B) and row (D) l / 16.  KM = 16: two blocks
