@@ -94,20 +94,32 @@ enum { VT_F64 = 0, VT_F32 = 1, VT_BF16 = 2 };
 // lines of 128 bytes that the 64 lanes of a slot touch, Q1 Laplacian, in
 // natural numbering (5.5: whole runs of neighbours) and reverse Cuthill-McKee
 // (8 to 12); short rows read by single slots gain either way
+//   60^3 natural                     13.1 / 11.8    9.2 /  8.7
+//   70^3 natural (FP32: 57 MB)       18.9 / 19.0   13.3 / 12.1
+//   76^3 natural (73 MB)             22.5 / 23.2   14.9 / 15.1
 //   80^3 natural                     25.7 / 27.7   16.9 / 17.5   12.8 / 13.5
+//   84^3 natural                     30.3 / 30.1   19.5 / 21.2
 //   96^3 natural                     45.1 / 43.7   26.7 / 28.0   20.1 / 22.3
+//   105^3 natural (FP32: 192 MB)     60.0 / 60.7   33.3 / 35.0
 //   110^3 natural                    69.9 / 69.8   38.8 / 39.0   29.2 / 30.5
+//   118^3 natural                    87.3 / 84.5   48.2 / 47.3
 //   126^3 natural                   106.3 / 101.6  58.6 / 55.9   43.5 / 42.3
 //   70^3                             19.5 / 19.6   15.0 / 12.5   11.6 /  9.5
 //   90^3                             37.7 / 37.2   25.9 / 24.0   19.5 / 18.9
+// refined solves with FP32 products (ms; 192 iterations), natural numbering
+//   70^3  2.58 / 2.70   80^3  3.10 / 3.21   88^3  3.75 / 3.84
+//   96^3  4.50 / 4.49  105^3  5.57 / 5.53  118^3  7.80 / 7.28
 constexpr int32_t kStageMax = 1280;     // columns of the widest group,
 constexpr int32_t kStageMaxOwn = 1023;  //   FP64 with rows of their own
 constexpr double kStageShared = 1.5;    // rows per pattern from which rows
                                         //   count as sharing
 constexpr double kStageMost = 0.45;     // columns per slot
 constexpr double kStageSlots = 4.5;     // mean slots per lane
-constexpr double kStageLines = 7.5;     // BF16 with rows of their own, read
-                                        //   by pairs: lines per slot
+constexpr double kStageLines = 7.5;     // lines per slot of rows of their own
+                                        //   read by pairs; below, BF16
+                                        //   gathers per slot, and FP32
+constexpr double kStageRunsFrom = 64e6; //   where slots of 6 bytes take so
+constexpr double kStageRunsTo = 180e6;  //   much
 inline bool stage_pays(double slots, double lanes)
 {
     return slots >= kStageSlots * lanes;
@@ -119,8 +131,11 @@ inline int32_t stage_forms(int32_t widest, double columns, double slots,
     if (widest > kStageMax || columns > kStageMost * slots) return 0;
     const bool shared = rows >= kStageShared * patterns;
     const bool f64 = shared || widest <= kStageMaxOwn;
-    const bool bf16 = shared || vec == 1 || 64 * lines >= kStageLines * slots;
-    return 1 << VT_F32 | (f64 ? 1 << VT_F64 : 0) | (bf16 ? 1 << VT_BF16 : 0);
+    const bool runs = !shared && vec > 1 && 64 * lines < kStageLines * slots;
+    const bool f32 = !runs || 6 * slots < kStageRunsFrom ||
+                     6 * slots > kStageRunsTo;
+    return (f32 ? 1 << VT_F32 : 0) | (f64 ? 1 << VT_F64 : 0) |
+           (runs ? 0 : 1 << VT_BF16);
 }
 
 // Batch shape that a timed workgroup choice of cg_solve_batch_wg is kept for.

@@ -53,6 +53,28 @@ def test_runs_of_neighbours(orc, permute, bf16):
     assert info["relres"] <= 1e-8
 
 
+@pytest.mark.parametrize("n,f32", [(60, True), (77, False)])
+def test_float_runs_of_neighbours(orc, n, f32):
+    """The FP32 product of a Q1 Laplacian in natural numbering gathers per
+    slot where its slots take 64 to 180 MB."""
+    note("float runs n=%d" % n)
+    A = W.hex_q1(n, "laplace", seed=(94, 0), permute=False)
+    M = make(A, dtypes=fs.DT_F32)
+    assert fs.csr_info(M)["vec"] == 2
+    assert forms(M) & STAGED64 and bool(forms(M) & STAGED) == f32
+    x = np.random.default_rng(5).uniform(-1, 1, A.n_cols).astype(np.float32)
+    perm = fs.csr_get_perm(M)
+    R = CSR(A.n_rows, A.n_cols, A.rowptr, A.col, A.val.astype(np.float32).astype(np.float64))
+    xd = x.astype(np.float64)
+    bound = (27 + 8) * 2.0 ** -24 * orc.spmv_abs(R, xd)
+    y = host(fs.spmv_lowp(M, fs.DT_F32, dev(x[perm])))
+    assert np.all(np.abs(y - orc.spmv(R, xd)[perm]) <= bound[perm])
+    b = dev(np.random.default_rng(6).uniform(-1, 1, A.n_rows))
+    S = make(CSR(A.n_rows, A.n_cols, A.rowptr, A.col, shifted(A)))
+    X, info = fs.cg_solve(S, b, precision=fs.PREC_IR_F32)
+    assert info["relres"] <= 1e-8
+
+
 def shifted(A):
     """The values with twice the diagonal (positive definite)."""
     rows = np.repeat(np.arange(A.n_rows), np.diff(A.rowptr))

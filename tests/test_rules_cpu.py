@@ -49,6 +49,18 @@ def test_stage_forms(tmp_path, what, widest, columns, slots, rows, patterns, vec
     assert out == [str(forms)], what
 
 
+@pytest.mark.parametrize("slots,f32", [(1.06e7, True), (1.07e7, False), (2.99e7, False), (3.01e7, True)])
+@pytest.mark.parametrize("what,rows_per_pattern,vec,lines", [
+    ("runs of neighbours", 1, 2, 5.5), ("rows that share columns", 3, 2, 5.5), ("single slots", 1, 1, 5.5), ("no runs", 1, 2, 8)])
+def test_float_products_of_runs(tmp_path, what, rows_per_pattern, vec, lines, slots, f32):
+    """FP32 products of runs of neighbours gather per slot from 64 to 180 MB
+    of slots, the others never for that."""
+    out = run_cpp(tmp_path, ["rules.h"], 'std::printf("%%d\\n", stage_forms(300, %s, %s, %s, %s, %d, %s));' % (
+        0.35 * slots, slots, slots / 27, slots / 27 / rows_per_pattern, vec, lines * slots / 64))
+    runs = what == "runs of neighbours"
+    assert out == [str(F64 | (0 if runs else BF16) | (F32 if f32 or not runs else 0))], what
+
+
 def test_rows_too_short_to_stage(tmp_path):
     out = run_cpp(tmp_path, ["rules.h"], r"""
     for (int w : {1, 3, 4, 5, 7}) std::printf("%d ", int(stage_pays(64.0 * w, 64.0)));
